@@ -219,20 +219,19 @@ size_t cp_attn_partial_workspace_size(const cp_partial_desc* descs, int32_t n_de
  *   head_dim    must be 128 (else CP_ERR_UNSUPPORTED).
  *   softmax_scale  <= 0 selects 1/sqrt(head_dim) (the paper's 1/sqrt(d_h)).
  *   workspace   device buffer of workspace_bytes >= the size above; it is
- *               written by an asynchronous copy on `stream` and read by the
- *               kernel, so it must not be reused until the stream reaches
- *               this work.
+ *               written and read by the call's kernels on `stream`, so it
+ *               must not be reused until the stream is past this work.
  * The work list is planned on the host; the lists of the last 16 launches
  * are kept (keyed by every non-pointer field of the descriptors, the head
  * counts and the pinned workgroup shape, matched exactly), so a launch of
  * the same geometry with other buffers, such as the next layer's, reuses its
  * list instead of planning it again.
- * Each call stages the descriptor copy through pinned host memory owned by
- * the library (allocated on first use, kept until process exit), in a ring
- * of eight slots, and a small kernel on `stream` copies it into the
- * workspace: a call that finds its slot's previous copy not yet done blocks
- * the calling host thread on that copy's event (never on the whole device)
- * before reusing the slot.
+ * The descriptors and the work list of a small launch (up to 3.5 KB) are
+ * kernel arguments.  Larger tables are staged in pinned host memory owned by
+ * the library (allocated on first use, kept until process exit), a ring of
+ * eight slots, and a small kernel on `stream` copies them into the workspace:
+ * a call that finds its slot not yet read by its last copy blocks the calling
+ * host thread until that copy has run (never on the whole device).
  * Errors: CP_ERR_INVALID (shapes, plans, pointers, alignment, kv_rank),
  * CP_ERR_UNSUPPORTED (head_dim; a request with P + R > 2^30 tokens),
  * CP_ERR_CAPACITY (workspace), CP_ERR_HIP.

@@ -613,16 +613,44 @@ __device__ __forceinline__ void exact_softmax(Scores<NB>& s, float (&m_run)[NB],
 constexpr int kLoadsPerTile = 2;  // K and V loads of one tile per wave
 constexpr int kWaitVm(int n) { return 0x0F70 | n; }
 
-template <int NB>
+// Tables among the kernel's arguments (InlineTables): read through the
+// argument segment's own address, as scalar loads (an indexed array of a
+// by-value struct may be copied to scratch memory first).
+struct InlineArgs {
+  const DevDesc* descs;
+  const WorkItem* items;
+  PartialParams p;
+  InlineTables tables;
+};
+static_assert(sizeof(InlineArgs) <= 4096 - 256, "the kernel argument space");
+
+__device__ __forceinline__ const DevDesc* inline_desc(int i) {
+  typedef const __attribute__((address_space(4))) unsigned char* Args;
+  const Args t = (Args)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(InlineArgs, tables);
+  return (const DevDesc*)(t) + i;
+}
+
+__device__ __forceinline__ uint64_t inline_word(int n_descs, int i) {
+  typedef const __attribute__((address_space(4))) unsigned char* Args;
+  const Args t = (Args)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(InlineArgs, tables);
+  return ((const __attribute__((address_space(4))) uint64_t*)(t + n_descs * sizeof(DevDesc)))[i];
+}
+
+template <int NB, class... Tables>
 __global__ __launch_bounds__(64 * kWaves, 1) void attn_partial_kernel(const DevDesc* __restrict__ descs,
                                                                      const WorkItem* __restrict__ items,
-                                                                     PartialParams p) {
+                                                                     PartialParams p, Tables... tables) {
   // LDS: kBufs K tile buffers, then kBufs V tile buffers; tile t uses buffer
   // t % kBufs of each.
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kBufs * kTileBytes];
 
-  const WorkItem it = items[blockIdx.x];
-  const DevDesc& d = descs[it.desc];
+  constexpr bool kInline = sizeof...(Tables) != 0;
+  WorkItem it;
+  if constexpr (kInline)
+    it = item_of_inline(inline_word(p.n_descs, blockIdx.x));
+  else
+    it = items[blockIdx.x];
+  const DevDesc& d = kInline ? *inline_desc(it.desc) : descs[it.desc];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -983,14 +1011,21 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_partial_kernel(const DevD
 // rows_per_wg / 8 blocks per split item.
 constexpr int kMergeRowsPerBlock = 8;
 
+template <class... Tables>
 __global__ __launch_bounds__(256) void split_merge_kernel(const DevDesc* __restrict__ descs,
-                                                          const SplitItem* __restrict__ splits, PartialParams p) {
+                                                          const SplitItem* __restrict__ splits, PartialParams p,
+                                                          Tables... tables) {
+  constexpr bool kInline = sizeof...(Tables) != 0;
   const int blocks_per_item = p.rows_per_wg / kMergeRowsPerBlock;
   const size_t slot_bytes = piece_bytes(p.rows_per_wg), o_bytes = piece_o_bytes(p.rows_per_wg);
-  const SplitItem sp = splits[blockIdx.x / blocks_per_item];
+  SplitItem sp;
+  if constexpr (kInline)
+    sp = split_of_inline(inline_word(p.n_descs, p.n_items + blockIdx.x / blocks_per_item));
+  else
+    sp = splits[blockIdx.x / blocks_per_item];
+  const DevDesc& d = kInline ? *inline_desc(sp.desc) : descs[sp.desc];
   const int r = (blockIdx.x % blocks_per_item) * kMergeRowsPerBlock + (threadIdx.x >> 5);
   const int lane = threadIdx.x & 31;
-  const DevDesc& d = descs[sp.desc];
   // The row's place, as the attention kernel assigns it (block bi, query l16).
   const int bi = r >> 4, l16 = r & 15;
   const int qblocks_per_head = p.q_per_wg >> 4;
@@ -1034,27 +1069,35 @@ __global__ __launch_bounds__(256) void split_merge_kernel(const DevDesc* __restr
   if (lane == 0) d.lse[row * p.Hq + head] = lse;
 }
 
+int launched(const char* what) {
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? CP_OK : fail(CP_ERR_HIP, std::string(what) + hipGetErrorString(e));
+}
+
+// The attention kernel and, when items were split, their merge; `tables` is
+// empty (the tables are in device memory) or one InlineTables.
+template <class... Tables>
+int launch_tables(const PartialParams& p, hipStream_t stream, const Tables&... tables) {
+  const dim3 grid((unsigned)p.n_items), block(64 * kWaves);
+  if (p.rows_per_wg == kWaves * kBlockRows * 3)
+    hipLaunchKernelGGL((attn_partial_kernel<3, Tables...>), grid, block, 0, stream, p.descs, p.items, p, tables...);
+  else
+    hipLaunchKernelGGL((attn_partial_kernel<2, Tables...>), grid, block, 0, stream, p.descs, p.items, p, tables...);
+  int st = launched("cp_attn_partial launch: ");
+  if (st != CP_OK || p.n_splits == 0) return st;
+  const dim3 blocks((unsigned)p.n_splits * (unsigned)(p.rows_per_wg / kMergeRowsPerBlock));
+  hipLaunchKernelGGL((split_merge_kernel<Tables...>), blocks, dim3(256), 0, stream, p.descs, p.splits, p, tables...);
+  return launched("cp_attn_partial merge launch: ");
+}
+
 }  // namespace
 
 int launch_partial(const PartialParams& p, void* stream) {
   if (p.n_items == 0) return CP_OK;
-  if (p.rows_per_wg == kWaves * kBlockRows * 3)
-    hipLaunchKernelGGL(attn_partial_kernel<3>, dim3((unsigned)p.n_items), dim3(64 * kWaves), 0, (hipStream_t)stream,
-                       p.descs, p.items, p);
-  else if (p.rows_per_wg == kWaves * kBlockRows * 2)
-    hipLaunchKernelGGL(attn_partial_kernel<2>, dim3((unsigned)p.n_items), dim3(64 * kWaves), 0, (hipStream_t)stream,
-                       p.descs, p.items, p);
-  else
+  if (p.rows_per_wg != kWaves * kBlockRows * 3 && p.rows_per_wg != kWaves * kBlockRows * 2)
     return fail(CP_ERR_INVALID, "cp_attn_partial: unsupported workgroup shape");
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("cp_attn_partial launch: ") + hipGetErrorString(e));
-  if (p.n_splits > 0) {
-    const unsigned blocks = (unsigned)p.n_splits * (unsigned)(p.rows_per_wg / kMergeRowsPerBlock);
-    hipLaunchKernelGGL(split_merge_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, p.descs, p.splits, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("cp_attn_partial merge launch: ") + hipGetErrorString(e));
-  }
-  return CP_OK;
+  if (p.inl) return launch_tables(p, (hipStream_t)stream, *p.inl);
+  return launch_tables(p, (hipStream_t)stream);
 }
 
 }  // namespace cpattn

@@ -27,10 +27,12 @@
 #include <cstdlib>
 #include <cstring>
 #include <atomic>
+#include <chrono>
 #include <mutex>
 #include <numeric>
 #include <queue>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "internal.h"
@@ -666,12 +668,35 @@ Layout layout_of(const Plan& plan) {
   return l;
 }
 
-void pack_tables(const Plan& plan, const Layout& lay, std::vector<unsigned char>* host) {
-  host->assign(lay.pieces, 0);
-  std::memcpy(host->data(), plan.descs.data(), plan.descs.size() * sizeof(DevDesc));
-  std::memcpy(host->data() + lay.items, plan.items.data(), plan.items.size() * sizeof(WorkItem));
+void pack_tables(const Plan& plan, const Layout& lay, unsigned char* host) {
+  std::memcpy(host, plan.descs.data(), plan.descs.size() * sizeof(DevDesc));
+  std::memcpy(host + lay.items, plan.items.data(), plan.items.size() * sizeof(WorkItem));
   if (!plan.splits.empty())
-    std::memcpy(host->data() + lay.splits, plan.splits.data(), plan.splits.size() * sizeof(SplitItem));
+    std::memcpy(host + lay.splits, plan.splits.data(), plan.splits.size() * sizeof(SplitItem));
+}
+
+bool pack_inline(const Plan& plan, InlineTables* out) {
+  const size_t n = plan.items.size() + plan.splits.size();
+  if (plan.descs.size() > (size_t)kInlineDescs || plan.descs.size() * sizeof(DevDesc) + n * 8 > kInlineBytes) return false;
+  std::memcpy(out->bytes, plan.descs.data(), plan.descs.size() * sizeof(DevDesc));
+  unsigned char* at = out->bytes + plan.descs.size() * sizeof(DevDesc);
+  for (const WorkItem& w : plan.items) {
+    if (w.q_block >= kInlineQBlocks || w.head_group >= kInlineGroups || w.t_begin >= kInlineTile ||
+        w.t_end >= kInlineTile || w.piece >= kInlinePiece)
+      return false;
+    const uint64_t x = inline_item(w);
+    std::memcpy(at, &x, 8);
+    at += 8;
+  }
+  for (const SplitItem& s : plan.splits) {
+    if (s.q_block >= kInlineQBlocks || s.head_group >= kInlineGroups || s.first_piece >= kInlinePiece ||
+        s.n_pieces >= kInlinePieces)
+      return false;
+    const uint64_t x = inline_split(s);
+    std::memcpy(at, &x, 8);
+    at += 8;
+  }
+  return true;
 }
 
 PartialParams partial_params(const Plan& plan, const Layout& lay, unsigned char* ws, int32_t Hq, int32_t Hkv,
@@ -692,6 +717,7 @@ PartialParams partial_params(const Plan& plan, const Layout& lay, unsigned char*
   p.pieces = plan.n_pieces ? ws + lay.pieces : nullptr;
   p.splits = reinterpret_cast<const SplitItem*>(ws + lay.splits);
   p.n_splits = (int32_t)plan.splits.size();
+  p.n_descs = (int32_t)plan.descs.size();
   return p;
 }
 
@@ -702,32 +728,43 @@ namespace {
 // Pinned host staging for the descriptor/work-list upload, mapped into the
 // device's address space and coherent (the device reads it over the bus,
 // never from a cached copy): the upload kernel reads it (upload.hip).  A slot
-// is reused only after the upload that read it has completed (its event).
+// is reused only after the upload that read it is done with it: the kernel's
+// blocks write the words after the tables, or, where the upload was captured
+// into a graph, its event says so.
 struct Slot {
-  void* host = nullptr;
+  unsigned char* host = nullptr;
   void* mapped = nullptr;  // the same memory as the device addresses it
   size_t cap = 0;
   hipEvent_t ev = nullptr;
   int device = -1;
-  bool pending = false;
+  size_t words_at = 0;   // the pending upload's words
+  size_t n_words = 0;    // 0: none pending
+  bool ev_pending = false;
 };
 constexpr int kSlots = 8;
 std::mutex g_stage_mu;
 Slot g_slots[kSlots];
 int g_next_slot = 0;
 
-int stage_and_copy(const void* src, size_t bytes, void* dst, hipStream_t stream) {
-  std::lock_guard<std::mutex> lock(g_stage_mu);
+// Waits until the slot's pending upload has read it.
+int wait_slot(Slot& s) {
+  const uint32_t* done = reinterpret_cast<const uint32_t*>(s.host + s.words_at);
+  for (size_t i = 0; i < s.n_words; ++i)
+    for (int spins = 0; __atomic_load_n(done + i, __ATOMIC_ACQUIRE) == 0; ++spins)
+      if (spins > 1000) std::this_thread::sleep_for(std::chrono::microseconds(10));
+  s.n_words = 0;
+  if (s.ev_pending) {
+    const hipError_t e = hipEventSynchronize(s.ev);
+    if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventSynchronize: ") + hipGetErrorString(e));
+    s.ev_pending = false;
+  }
+  return CP_OK;
+}
+
+int record_slot(Slot& s, hipStream_t stream) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
-  Slot& s = g_slots[g_next_slot];
-  g_next_slot = (g_next_slot + 1) % kSlots;
-  if (s.pending) {
-    e = hipEventSynchronize(s.ev);
-    if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventSynchronize: ") + hipGetErrorString(e));
-    s.pending = false;
-  }
   if (s.ev && s.device != dev) {
     (void)hipEventDestroy(s.ev);
     s.ev = nullptr;
@@ -737,24 +774,46 @@ int stage_and_copy(const void* src, size_t bytes, void* dst, hipStream_t stream)
     if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventCreate: ") + hipGetErrorString(e));
     s.device = dev;
   }
-  if (s.cap < bytes) {
+  e = hipEventRecord(s.ev, stream);
+  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
+  s.ev_pending = true;
+  return CP_OK;
+}
+
+int stage_and_copy(const Plan& plan, const Layout& lay, void* dst, hipStream_t stream) {
+  const size_t bytes = lay.pieces;  // the tables; a multiple of 256
+  const size_t n_words = upload_blocks(bytes);
+  std::lock_guard<std::mutex> lock(g_stage_mu);
+  Slot& s = g_slots[g_next_slot];
+  g_next_slot = (g_next_slot + 1) % kSlots;
+  int st = wait_slot(s);
+  if (st != CP_OK) return st;
+  if (s.cap < bytes + 4 * n_words) {
     if (s.host) (void)hipHostFree(s.host);
     s.host = nullptr;
     s.mapped = nullptr;
     s.cap = 0;
-    const size_t cap = std::max<size_t>(bytes, 64 * 1024);
-    e = hipHostMalloc(&s.host, cap, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
+    const size_t cap = std::max<size_t>(bytes + 4 * n_words, 64 * 1024);
+    void* host = nullptr;
+    hipError_t e = hipHostMalloc(&host, cap, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
     if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipHostMalloc (staging): ") + hipGetErrorString(e));
+    s.host = static_cast<unsigned char*>(host);
     e = hipHostGetDevicePointer(&s.mapped, s.host, 0);
     if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipHostGetDevicePointer (staging): ") + hipGetErrorString(e));
     s.cap = cap;
   }
-  std::memcpy(s.host, src, bytes);
-  const int up = cpattn::launch_upload(dst, s.mapped, bytes, stream);
-  if (up != CP_OK) return up;
-  e = hipEventRecord(s.ev, stream);
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
-  s.pending = true;
+  pack_tables(plan, lay, s.host);
+  std::memset(s.host + bytes, 0, 4 * n_words);
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusNone;
+  }
+  st = cpattn::launch_upload(dst, s.mapped, bytes, stream);
+  if (st != CP_OK) return st;
+  if (capture != hipStreamCaptureStatusNone) return record_slot(s, stream);
+  s.words_at = bytes;
+  s.n_words = n_words;
   return CP_OK;
 }
 
@@ -792,14 +851,18 @@ extern "C" int cp_attn_partial(const cp_partial_desc* descs, int32_t n_descs, in
     if (!aligned(workspace, 256)) return fail(CP_ERR_INVALID, "cp_attn_partial: workspace must be 256-byte aligned");
     if (workspace_bytes < lay.total)
       return fail(CP_ERR_CAPACITY, "cp_attn_partial: workspace needs " + std::to_string(lay.total) + " bytes");
-    // Only the tables are uploaded; the piece slots are written by the kernel.
-    std::vector<unsigned char> host;
-    pack_tables(plan, lay, &host);
-    st = stage_and_copy(host.data(), lay.pieces, workspace, (hipStream_t)stream);
-    if (st != CP_OK) return st;
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.f / std::sqrt((float)head_dim);
-    st = launch_partial(partial_params(plan, lay, static_cast<unsigned char*>(workspace), n_heads_q, n_heads_kv, scale),
-                        stream);
+    PartialParams p =
+        partial_params(plan, lay, static_cast<unsigned char*>(workspace), n_heads_q, n_heads_kv, scale);
+    InlineTables inl;
+    if (pack_inline(plan, &inl)) {
+      p.inl = &inl;
+    } else {
+      // Only the tables are uploaded; the piece slots are written by the kernel.
+      st = stage_and_copy(plan, lay, workspace, (hipStream_t)stream);
+      if (st != CP_OK) return st;
+    }
+    st = launch_partial(p, stream);
     if (st == CP_OK) clear_error();
     return st;
   });

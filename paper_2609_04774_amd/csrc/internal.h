@@ -110,6 +110,60 @@ struct SplitItem {
 __host__ __device__ constexpr size_t piece_o_bytes(int rows) { return (size_t)rows * kHeadDim * 4; }
 __host__ __device__ constexpr size_t piece_bytes(int rows) { return piece_o_bytes(rows) + (size_t)rows * 4; }
 
+// The tables of a small launch, passed with the kernel's arguments: the
+// descriptors, then one 64-bit word per work item, then one per split item.
+// A launch whose tables go through the workspace runs a copy kernel first
+// (upload.hip), which costs a small launch 5 us and more; arguments are there
+// when the kernel starts.  4 KB is the argument space a launch may count on,
+// the parameters and the compiler's implicit arguments (256 bytes) included.
+constexpr size_t kInlineBytes = 3584;
+struct InlineTables {
+  alignas(16) unsigned char bytes[kInlineBytes];
+};
+
+// Fields of the words (bits): descriptor 5, chunk 1, query block 13, head
+// group 7, then an item's first tile 13, end tile 13 (all ones: the whole
+// walk), piece 12 (all ones: none), or a split item's first piece 12, pieces 7.
+// Launches with a larger value in any field use the workspace.
+constexpr int kInlineDescs = 1 << 5, kInlineQBlocks = 1 << 13, kInlineGroups = 1 << 7;
+constexpr int kInlineTile = (1 << 13) - 1, kInlinePiece = (1 << 12) - 1, kInlinePieces = 1 << 7;
+
+__host__ __device__ inline uint64_t inline_place(int desc, int chunk, int q_block, int head_group) {
+  return (uint64_t)desc | (uint64_t)chunk << 5 | (uint64_t)q_block << 6 | (uint64_t)head_group << 19;
+}
+__host__ __device__ inline uint64_t inline_item(const WorkItem& w) {
+  return inline_place(w.desc, w.chunk, w.q_block, w.head_group) | (uint64_t)w.t_begin << 26 |
+         (uint64_t)(w.t_end < 0 ? kInlineTile : w.t_end) << 39 |
+         (uint64_t)(w.piece < 0 ? kInlinePiece : w.piece) << 52;
+}
+__host__ __device__ inline uint64_t inline_split(const SplitItem& s) {
+  return inline_place(s.desc, s.chunk, s.q_block, s.head_group) | (uint64_t)s.first_piece << 26 |
+         (uint64_t)s.n_pieces << 38;
+}
+__host__ __device__ inline WorkItem item_of_inline(uint64_t x) {
+  WorkItem w;
+  w.desc = (int)(x & 31);
+  w.chunk = (int)(x >> 5) & 1;
+  w.q_block = (int)(x >> 6) & (kInlineQBlocks - 1);
+  w.head_group = (int)(x >> 19) & (kInlineGroups - 1);
+  w.t_begin = (int)(x >> 26) & kInlineTile;
+  const int t_end = (int)(x >> 39) & kInlineTile, piece = (int)(x >> 52);
+  w.t_end = t_end == kInlineTile ? -1 : t_end;
+  w.piece = piece == kInlinePiece ? -1 : piece;
+  w.reserved = 0;
+  return w;
+}
+__host__ __device__ inline SplitItem split_of_inline(uint64_t x) {
+  SplitItem s;
+  s.desc = (int)(x & 31);
+  s.chunk = (int)(x >> 5) & 1;
+  s.q_block = (int)(x >> 6) & (kInlineQBlocks - 1);
+  s.head_group = (int)(x >> 19) & (kInlineGroups - 1);
+  s.first_piece = (int)(x >> 26) & kInlinePiece;
+  s.n_pieces = (int)(x >> 38) & (kInlinePieces - 1);
+  return s;
+}
+
 struct PartialParams {
   const DevDesc* descs;
   const WorkItem* items;
@@ -125,13 +179,20 @@ struct PartialParams {
   unsigned char* pieces;  // piece slots (kPieceBytes each), or null when nothing is split
   const SplitItem* splits;
   int32_t n_splits;
+  int32_t n_descs;
+  const InlineTables* inl;  // host: the launch's tables as arguments (descs, items and splits unused), or null
 };
 
 int launch_partial(const PartialParams& p, void* stream);
 
 // Copies `bytes` (a multiple of 16) from pinned host memory mapped into the
 // device's address space to device memory, with a kernel on `stream`
-// (upload.hip).
+// (upload.hip).  The source is followed by upload_blocks(bytes) 32-bit words:
+// block b of the kernel writes 1 to word b when it has read its part of the
+// source (not when the stream is being captured: a graph may run the kernel
+// again after the memory has another use).
+constexpr size_t kUploadBlockBytes = 4096;
+inline size_t upload_blocks(size_t bytes) { return (bytes + kUploadBlockBytes - 1) / kUploadBlockBytes; }
 int launch_upload(void* dst, const void* src, size_t bytes, void* stream);
 
 // Host planning of one cp_attn_partial launch (cp_attn.cpp), shared by the
@@ -162,7 +223,9 @@ struct Layout {
   size_t items, splits, pieces, total;
 };
 Layout layout_of(const Plan& plan);
-void pack_tables(const Plan& plan, const Layout& lay, std::vector<unsigned char>* host);
+void pack_tables(const Plan& plan, const Layout& lay, unsigned char* host);
+// The plan's tables in argument form; false if they do not fit it.
+bool pack_inline(const Plan& plan, InlineTables* out);
 PartialParams partial_params(const Plan& plan, const Layout& lay, unsigned char* ws, int32_t Hq, int32_t Hkv,
                              float scale);
 

@@ -86,8 +86,8 @@ extern "C" int cp_attn_partial_noalloc(const cp_partial_desc* descs, int32_t n_d
     unsigned char* ws = nullptr;
     int st = scratch_of_current_device(&ws);
     if (st != CP_OK) return st;
-    std::vector<unsigned char> host;
-    pack_tables(plan, lay, &host);
+    std::vector<unsigned char> host(lay.pieces);
+    pack_tables(plan, lay, host.data());
     // The scratch is shared by every call on this GPU: wait until the stream's
     // earlier work (an earlier call's kernels among it) is done before
     // overwriting the tables, then copy them from pageable host memory (a

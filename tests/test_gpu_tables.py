@@ -1,0 +1,89 @@
+"""How a launch's tables reach the kernel: among its arguments when they are
+small, else through pinned staging that is reused after eight launches.
+Either way the results are those of cp_attn_partial_noalloc, which copies its
+tables itself and plans the same list, bit for bit."""
+
+import pytest
+import torch
+
+import gpu_cases as gc
+from gpu_cases import DEV, Problem
+from paper_2609_04774_amd import cpattn as cp
+
+pytestmark = pytest.mark.gpu
+
+
+def _launch(R, Hq, Hkv, seed, C=1, n_descs=1):
+    prob = Problem(R, 0, C, Hq, Hkv, seed)
+    dv = prob.dev()
+    plan, rows = cp.shard_plan(0, R, C, 0)
+    q = dv["q"][torch.as_tensor(rows, device=DEV)].contiguous()
+    outs = [gc.alloc_out(plan.n_rows, Hq) for _ in range(2 * n_descs)]
+    descs = [cp.make_desc(plan, q, dv["k"], dv["v"], o, lse) for o, lse in outs]
+    return descs[:n_descs], descs[n_descs:], outs, n_descs
+
+
+def _compare(launch, what):
+    _, _, outs, n = launch
+    for i in range(n):
+        assert torch.equal(outs[i][0], outs[n + i][0]) and torch.equal(outs[i][1], outs[n + i][1]), what
+
+
+# One head per KV head: a work item is 256 (or 384) rows of one head, so the
+# item count is Hq * ceil(R / rows).  One descriptor leaves room for 424 words.
+@pytest.mark.parametrize("rows", [256, 384])
+@pytest.mark.parametrize("R,H,n_descs", [(1, 1, 1), (60, 424, 1), (60, 425, 1), (400, 106, 2), (40, 8, 17),
+                                         (40, 8, 33)])
+def test_tables_on_both_sides_of_the_argument_space(rows, R, H, n_descs):
+    try:
+        cp.set_workgroup_rows(rows)
+        launch = _launch(R, H, H, 11, n_descs=n_descs)
+        gc.run_partials(launch[0], H, H)
+        cp.attn_partial_noalloc(launch[1], H, H)
+        torch.cuda.synchronize()
+    finally:
+        cp.set_workgroup_rows(0)
+    _compare(launch, f"R {R}, heads {H}, descriptors {n_descs}")
+
+
+def test_staging_is_reused_in_order():
+    """Twenty launches of different tables in flight at once, of sizes that
+    make the staging slots grow and be written again while earlier launches
+    have yet to read theirs."""
+    launches, ws = [], []
+    for i in range(20):
+        H = 425 + 97 * ((7 * i) % 20)
+        launches.append((H, _launch(33 + i, H, H, 100 + i)))
+        ws.append(gc.new_workspace(launches[-1][1][0], H, H))
+    torch.cuda.synchronize()
+    torch.cuda._sleep(20_000_000)
+    for (H, launch), w in zip(launches, ws):
+        cp.attn_partial(launch[0], H, H, w)
+    for H, launch in launches:
+        cp.attn_partial_noalloc(launch[1], H, H)
+    torch.cuda.synchronize()
+    for H, launch in launches:
+        _compare(launch, f"{H} heads")
+
+
+@pytest.mark.parametrize("H", [8, 500])
+def test_a_captured_launch_replays(H):
+    launch = _launch(200, H, H, 21)
+    ws = gc.new_workspace(launch[0], H, H)
+    other = _launch(77, 8, 8, 22)
+    other_ws = gc.new_workspace(other[0], 8, 8)
+    for _ in range(8):  # every staging slot is allocated before the capture
+        cp.attn_partial(launch[0], H, H, ws)
+    cp.attn_partial_noalloc(launch[1], H, H)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cp.attn_partial(launch[0], H, H, ws)
+    for _ in range(3):
+        launch[2][0][0].zero_()
+        launch[2][0][1].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        _compare(launch, f"replay, {H} heads")
+        cp.attn_partial(other[0], 8, 8, other_ws)
+    torch.cuda.synchronize()
