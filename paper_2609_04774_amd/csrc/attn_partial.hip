@@ -1007,16 +1007,30 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_partial_kernel(const DevD
 // same rows): LSE = M + ln sum_k e^{LSE_k - M}, O = sum_k e^{LSE_k - LSE} O_k,
 // a piece with LSE_k = -inf weighing 0 (and not read).  Each row of the item
 // is written to the descriptor's output where the unsplit item would have
-// written it.  32 lanes per row (float4 each), 8 rows per 256-thread block,
-// rows_per_wg / 8 blocks per split item.
-constexpr int kMergeRowsPerBlock = 8;
+// written it.
+//
+// Bound by latency when few rows have many pieces (a short suffix behind a
+// long prefix), by memory when many rows have two or three (balance cuts).  A
+// row takes kLanes lanes: 64, whose halves (32 lanes, float4 each) take every
+// other piece, for many pieces, or one half.  The LSEs are one load, a piece
+// per lane, reduced across the lanes; kMergeInFlight pieces of O per half are
+// loaded before any is used.  Measured as whole calls, against 32 lanes that
+// read one LSE and one piece after the other: 8 heads x 121 rows behind 19648
+// keys (62 pieces per item) 70.8 -> 28.6 us, 33.7 with one half per row; 100
+// rows of 64 heads (11 pieces) 39.2 -> 30.2, 30.8 with a wave per row; two
+// pieces per item (the 32K shard) unchanged.
+constexpr int kMergeThreads = 256;
+constexpr int kMergeInFlight = 4;
+constexpr int kWaveMergePieces = 16;  // pieces per item from which a row takes a wave
 
-template <class... Tables>
-__global__ __launch_bounds__(256) void split_merge_kernel(const DevDesc* __restrict__ descs,
+template <int kLanes, class... Tables>
+__global__ __launch_bounds__(kMergeThreads) void split_merge_kernel(const DevDesc* __restrict__ descs,
                                                           const SplitItem* __restrict__ splits, PartialParams p,
                                                           Tables... tables) {
   constexpr bool kInline = sizeof...(Tables) != 0;
-  const int blocks_per_item = p.rows_per_wg / kMergeRowsPerBlock;
+  constexpr int kRows = kMergeThreads / kLanes;  // rows per block
+  constexpr int kHalves = kLanes / 32;
+  const int blocks_per_item = p.rows_per_wg / kRows;
   const size_t slot_bytes = piece_bytes(p.rows_per_wg), o_bytes = piece_o_bytes(p.rows_per_wg);
   SplitItem sp;
   if constexpr (kInline)
@@ -1024,8 +1038,8 @@ __global__ __launch_bounds__(256) void split_merge_kernel(const DevDesc* __restr
   else
     sp = splits[blockIdx.x / blocks_per_item];
   const DevDesc& d = kInline ? *inline_desc(sp.desc) : descs[sp.desc];
-  const int r = (blockIdx.x % blocks_per_item) * kMergeRowsPerBlock + (threadIdx.x >> 5);
-  const int lane = threadIdx.x & 31;
+  const int r = (blockIdx.x % blocks_per_item) * kRows + threadIdx.x / kLanes;
+  const int lane = threadIdx.x % kLanes, col = lane & 31, half = lane >> 5;
   // The row's place, as the attention kernel assigns it (block bi, query l16).
   const int bi = r >> 4, l16 = r & 15;
   const int qblocks_per_head = p.q_per_wg >> 4;
@@ -1034,29 +1048,65 @@ __global__ __launch_bounds__(256) void split_merge_kernel(const DevDesc* __restr
   const int qrel = (bi % qblocks_per_head) * 16 + l16;
   const int64_t qb0 = (int64_t)sp.q_block * p.q_per_wg;
   const int64_t q_len = sp.chunk ? d.q_len[1] : d.q_len[0];
-  if (qb0 + qrel >= q_len) return;
+  if (qb0 + qrel >= q_len) return;  // all lanes of the row
   const int64_t row = (sp.chunk ? d.o_off[1] : d.o_off[0]) + qb0 + qrel;
+  const unsigned char* slots = p.pieces + (size_t)sp.first_piece * slot_bytes;
 
+  // Pieces lane, lane + kLanes, ... of the up to 64.
+  constexpr int kPer = 64 / kLanes;
+  float l[kPer], w[kPer];
   float m = -INFINITY;
-  for (int k = 0; k < sp.n_pieces; ++k) {
-    const unsigned char* slot = p.pieces + (size_t)(sp.first_piece + k) * slot_bytes;
-    m = fmaxf(m, reinterpret_cast<const float*>(slot + o_bytes)[r]);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int k = lane + j * kLanes;
+    l[j] = k < sp.n_pieces ? reinterpret_cast<const float*>(slots + (size_t)k * slot_bytes + o_bytes)[r] : -INFINITY;
+    m = fmaxf(m, l[j]);
   }
+#pragma unroll
+  for (int k = 1; k < kLanes; k *= 2) m = fmaxf(m, __shfl_xor(m, k));
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   float lse = -INFINITY;
   if (m != -INFINITY) {
     float total = 0.f;
-    for (int k = 0; k < sp.n_pieces; ++k) {
-      const unsigned char* slot = p.pieces + (size_t)(sp.first_piece + k) * slot_bytes;
-      const float lk = reinterpret_cast<const float*>(slot + o_bytes)[r];
-      if (lk == -INFINITY) continue;
-      const float w = expf(lk - m);
-      total += w;
-      const float4 v = reinterpret_cast<const float4*>(slot)[(size_t)r * (kHeadDim / 4) + lane];
-      acc.x += w * v.x;
-      acc.y += w * v.y;
-      acc.z += w * v.z;
-      acc.w += w * v.w;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      w[j] = l[j] == -INFINITY ? 0.f : expf(l[j] - m);
+      total += w[j];
+    }
+#pragma unroll
+    for (int k = 1; k < kLanes; k *= 2) total += __shfl_xor(total, k);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int end = min(sp.n_pieces - j * kLanes, kLanes);
+      for (int k0 = 0; k0 < end; k0 += kHalves * kMergeInFlight) {
+        float4 v[kMergeInFlight];
+        float wk[kMergeInFlight];
+#pragma unroll
+        for (int i = 0; i < kMergeInFlight; ++i) {
+          const int k = k0 + kHalves * i + half;
+          v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+          wk[i] = __shfl(w[j], k, kLanes);
+          const float lk = __shfl(l[j], k, kLanes);
+          if (k < end && lk != -INFINITY)
+            v[i] = reinterpret_cast<const float4*>(slots + (size_t)(k + j * kLanes) *
+                                                               slot_bytes)[(size_t)r * (kHeadDim / 4) + col];
+          else
+            wk[i] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < kMergeInFlight; ++i) {
+          acc.x += wk[i] * v[i].x;
+          acc.y += wk[i] * v[i].y;
+          acc.z += wk[i] * v[i].z;
+          acc.w += wk[i] * v[i].w;
+        }
+      }
+    }
+    if (kHalves == 2) {
+      acc.x += __shfl_xor(acc.x, 32);
+      acc.y += __shfl_xor(acc.y, 32);
+      acc.z += __shfl_xor(acc.z, 32);
+      acc.w += __shfl_xor(acc.w, 32);
     }
     const float inv = 1.f / total;
     acc.x *= inv;
@@ -1065,7 +1115,7 @@ __global__ __launch_bounds__(256) void split_merge_kernel(const DevDesc* __restr
     acc.w *= inv;
     lse = m + logf(total);
   }
-  reinterpret_cast<float4*>(d.o + (row * p.Hq + head) * kHeadDim)[lane] = acc;
+  if (half == 0) reinterpret_cast<float4*>(d.o + (row * p.Hq + head) * kHeadDim)[col] = acc;
   if (lane == 0) d.lse[row * p.Hq + head] = lse;
 }
 
@@ -1085,8 +1135,14 @@ int launch_tables(const PartialParams& p, hipStream_t stream, const Tables&... t
     hipLaunchKernelGGL((attn_partial_kernel<2, Tables...>), grid, block, 0, stream, p.descs, p.items, p, tables...);
   int st = launched("cp_attn_partial launch: ");
   if (st != CP_OK || p.n_splits == 0) return st;
-  const dim3 blocks((unsigned)p.n_splits * (unsigned)(p.rows_per_wg / kMergeRowsPerBlock));
-  hipLaunchKernelGGL((split_merge_kernel<Tables...>), blocks, dim3(256), 0, stream, p.descs, p.splits, p, tables...);
+  const bool wave = p.n_pieces >= (int64_t)kWaveMergePieces * p.n_splits;
+  const dim3 blocks((unsigned)p.n_splits * (unsigned)(p.rows_per_wg / (kMergeThreads / (wave ? 64 : 32))));
+  if (wave)
+    hipLaunchKernelGGL((split_merge_kernel<64, Tables...>), blocks, dim3(kMergeThreads), 0, stream, p.descs, p.splits,
+                       p, tables...);
+  else
+    hipLaunchKernelGGL((split_merge_kernel<32, Tables...>), blocks, dim3(kMergeThreads), 0, stream, p.descs, p.splits,
+                       p, tables...);
   return launched("cp_attn_partial merge launch: ");
 }
 

@@ -718,6 +718,7 @@ PartialParams partial_params(const Plan& plan, const Layout& lay, unsigned char*
   p.splits = reinterpret_cast<const SplitItem*>(ws + lay.splits);
   p.n_splits = (int32_t)plan.splits.size();
   p.n_descs = (int32_t)plan.descs.size();
+  p.n_pieces = plan.n_pieces;
   return p;
 }
 

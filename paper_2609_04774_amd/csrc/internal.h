@@ -180,6 +180,7 @@ struct PartialParams {
   const SplitItem* splits;
   int32_t n_splits;
   int32_t n_descs;
+  int64_t n_pieces;
   const InlineTables* inl;  // host: the launch's tables as arguments (descs, items and splits unused), or null
 };
 
