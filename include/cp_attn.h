@@ -193,15 +193,14 @@ typedef struct cp_partial_desc {
 /*
  * Sizing call of cp_attn_partial (Sec. 2.1, 2.2 partial attention; the
  * workspace itself is a library interface, not from the paper).
- * Device workspace bytes cp_attn_partial needs for this descriptor set: the
- * device copy of the descriptors and the scheduled work list, and, when the
- * set has few work items with long key walks (a short suffix over a long
- * cached prefix) or long items that do not divide evenly among the compute
- * units, one slot of rows x (128 + 1) fp32 per piece the walks are split
- * into (rows = 256 or 384, the launch's workgroup size; about a thousand
- * pieces at most).  Deterministic in the descriptors, the head counts and
- * the cp_set_workgroup_rows setting.  0 on invalid arguments (and
- * cp_last_error says why).
+ * Device workspace bytes cp_attn_partial uses for this descriptor set: the
+ * device copy of the descriptors and the scheduled work list, and, when key
+ * walks are cut into pieces (few work items, or items that do not divide
+ * evenly among the compute units), one slot of rows x (128 + 1) fp32 per piece
+ * (rows = 256 or 384, the launch's workgroup size; about a thousand pieces at
+ * most).  Deterministic in the descriptors, the head counts and the
+ * cp_set_workgroup_rows setting.  0 on invalid arguments (and cp_last_error
+ * says why).
  */
 size_t cp_attn_partial_workspace_size(const cp_partial_desc* descs, int32_t n_descs,
                                       int32_t n_heads_q, int32_t n_heads_kv);
@@ -218,9 +217,11 @@ size_t cp_attn_partial_workspace_size(const cp_partial_desc* descs, int32_t n_de
  *   n_heads_q, n_heads_kv  Hq and Hkv, Hq % Hkv == 0.
  *   head_dim    must be 128 (else CP_ERR_UNSUPPORTED).
  *   softmax_scale  <= 0 selects 1/sqrt(head_dim) (the paper's 1/sqrt(d_h)).
- *   workspace   device buffer of workspace_bytes >= the size above; it is
- *               written and read by the call's kernels on `stream`, so it
- *               must not be reused until the stream is past this work.
+ *   workspace   device buffer of workspace_bytes >= the size above (a smaller
+ *               one is taken when fewer, longer pieces, or none, fit it; the
+ *               result is the same attention); it is written and read by the
+ *               call's kernels on `stream`, so it must not be reused until the
+ *               stream is past this work.
  * The work list is planned on the host; the lists of the last 16 launches
  * are kept (keyed by every non-pointer field of the descriptors, the head
  * counts and the pinned workgroup shape, matched exactly), so a launch of
@@ -247,8 +248,9 @@ int cp_attn_partial(const cp_partial_desc* descs, int32_t n_descs, int32_t n_hea
  * larger shares each K/V tile between more rows, the smaller fills the
  * compute units better when the launch has few or evenly long work items --
  * and by default (rows = 0) the host plan picks the one whose simulated
- * schedule ends first.  rows = 256 or 384 pins that shape for every later
- * call in the process (reproducible timings, tests of each kernel shape);
+ * schedule ends first, the pieces walks are cut into among its choices.
+ * rows = 256 or 384 pins that shape, with one fixed rule for the pieces, for
+ * every later call in the process (reproducible timings, tests of each shape);
  * results agree within rounding either way.  Process-wide; takes effect at
  * the next call.
  * Errors: CP_ERR_INVALID for any other value.

@@ -9,17 +9,17 @@
 // group on the same XCD: the workgroups streaming one head's K/V share that
 // XCD's L2.
 //
-// Split key walks.  When a launch has few work items (a short suffix over a
-// long cached prefix: few query rows, many keys each), the GPU's 256 compute
-// units would mostly idle.  Then each item's walk of key tiles is cut into
-// pieces of at least kMinPieceTiles tiles, aiming at about kTargetPieces
-// pieces in all; each piece is its own workgroup and writes a partial result
-// (O, LSE over its keys) to the workspace, and split_merge combines an item's
-// pieces exactly (the same log-sum-exp combination as cp_attn_merge).
+// Cut key walks.  A launch whose work items do not fill the 256 compute units
+// evenly (few items, or items of very different lengths) has some of its walks
+// of key tiles cut into pieces; each piece is its own workgroup and writes a
+// partial result (O, LSE over its keys) to the workspace, and split_merge
+// combines an item's pieces exactly (the same log-sum-exp combination as
+// cp_attn_merge).
 //
-// Workgroup shape.  The attention kernel runs 256- or 384-row workgroups; the
-// work list is built for both and the one whose simulated schedule ends first
-// is launched (balance cuts and the estimate below).
+// Choice.  The attention kernel runs 256- or 384-row workgroups.  For each
+// shape the uncut list, lists cut to a longest piece and, for long walks, the
+// balance cuts are timed by a simulation of the dispatch (below), and the one
+// that ends first is launched.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -157,9 +157,12 @@ int to_dev(const cp_partial_desc& x, int idx, DevDesc* out) {
   return CP_OK;
 }
 
-constexpr int64_t kSplitBelowItems = 512;  // split only launches with fewer non-empty items
-constexpr int64_t kMinPieceTiles = 32;     // 1024 keys: the prologue and merge stay small
+constexpr int64_t kMinPieceTiles = 3;      // the shortest piece of any list: the kernel's loads run five tiles ahead
 constexpr int64_t kMaxPieces = 64;
+// A pinned shape (cp_set_workgroup_rows) keeps one fixed rule for launches of
+// few items: pieces of at least kPinnedMinTiles, aiming at the target count.
+constexpr int64_t kPinnedBelowItems = 512;
+constexpr int64_t kPinnedMinTiles = 32;
 constexpr int kComputeUnits = 256;         // 8 XCDs x 32 compute units
 constexpr int64_t kItemSetupTiles = 16;    // a workgroup's set-up and stores, in tile times
 constexpr int64_t kMinBalancePiece = 256;  // tiles of the smaller part of a balance cut
@@ -371,59 +374,80 @@ int64_t item_keys(const DevDesc& d, int chunk, int64_t qb, int q_per_wg) {
   return keys;
 }
 
+// Query blocks of every descriptor and chunk for one workgroup shape, with
+// their tile counts; each is one work item per head group.
+struct Block {
+  int32_t desc, chunk, q_block;
+  int64_t keys, tiles;
+};
+
+struct Blocks {
+  Shape shape;
+  int n_groups;
+  std::vector<Block> list;
+  int64_t nonempty = 0, all_tiles = 0, max_tiles = 0;  // items with a tile; tiles of all items; the longest
+};
+
+Blocks list_blocks(const std::vector<DevDesc>& descs, int32_t Hq, int32_t Hkv, int rows) {
+  Blocks b;
+  b.shape = shape_for(Hq, Hkv, rows);
+  b.n_groups = Hkv * b.shape.groups_per_kv;
+  const int q_per_wg = b.shape.q_per_wg;
+  for (size_t i = 0; i < descs.size(); ++i) {
+    const DevDesc& d = descs[i];
+    for (int c = 0; c < 2; ++c)
+      for (int64_t qb = 0; qb * q_per_wg < d.q_len[c]; ++qb) {
+        const int64_t tiles = item_tiles(d, c, qb, q_per_wg);
+        b.list.push_back(Block{(int32_t)i, c, (int32_t)qb, item_keys(d, c, qb, q_per_wg), tiles});
+        if (tiles > 0) b.nonempty += b.n_groups;
+        b.all_tiles += tiles * b.n_groups;
+        b.max_tiles = std::max(b.max_tiles, tiles);
+      }
+  }
+  return b;
+}
+
+// Pieces of a walk of `tiles` cut to at most `cap` tiles each (in equal parts,
+// kMaxPieces at most).
+int64_t pieces_at(int64_t tiles, int64_t cap) { return std::max<int64_t>(1, std::min(kMaxPieces, (tiles + cap - 1) / cap)); }
+
+// The head groups of one schedule: with the groups a multiple of the XCDs,
+// each XCD's list is its own schedule on its 32 compute units, and all eight
+// are alike; otherwise the lists share the units (the interleave in plan_items
+// moves items between XCDs) and one schedule over all of them is the closer
+// model.
+int schedules_of(int n_groups) { return n_groups % kXcds == 0 ? kXcds : 1; }
+
 // The work list of one launch for one workgroup shape: items, split items and
-// piece count into *out (whose descriptors are set).
-int plan_items(int32_t Hq, int32_t Hkv, int rows, int64_t target_pieces, Plan* out) {
-  out->shape = shape_for(Hq, Hkv, rows);
-  const Shape& sh = out->shape;
-  const int n_descs = (int)out->descs.size();
-  const int n_groups = Hkv * sh.groups_per_kv;
+// piece count into *out (whose descriptors are set).  cap > 0: every walk cut
+// to at most that many tiles; cap = 0: balance cuts where they pay (few items
+// with a pinned shape: equal pieces, see kPinnedBelowItems).
+int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap, Plan* out) {
   struct Cand {
     int64_t cost;
     WorkItem w;
   };
-  // Query blocks of every descriptor and chunk, with their tile counts.
-  struct Block {
-    int32_t desc, chunk, q_block;
-    int64_t keys, tiles;
-  };
-  std::vector<Block> blocks;
-  int64_t nonempty = 0, all_tiles = 0, max_tiles = 0;
-  for (int i = 0; i < n_descs; ++i) {
-    const DevDesc& d = out->descs[i];
-    for (int c = 0; c < 2; ++c) {
-      if (d.q_len[c] == 0) continue;
-      const int64_t nqb = (d.q_len[c] + sh.q_per_wg - 1) / sh.q_per_wg;
-      for (int64_t qb = 0; qb < nqb; ++qb) {
-        const int64_t tiles = item_tiles(d, c, qb, sh.q_per_wg);
-        blocks.push_back(Block{i, c, (int32_t)qb, item_keys(d, c, qb, sh.q_per_wg), tiles});
-        if (tiles > 0) nonempty += n_groups;
-        all_tiles += tiles * n_groups;
-        max_tiles = std::max(max_tiles, tiles);
-      }
-    }
-  }
-  // Splitting pays when the longest walk is long against the piece size (the
-  // pieces' set-up and the merge pass are not free).
-  int64_t piece_tiles = 0;  // 0: no splitting in this launch
-  if (target_pieces > 0 && nonempty > 0 && nonempty < kSplitBelowItems && max_tiles >= 4 * kMinPieceTiles)
-    piece_tiles = std::max<int64_t>(kMinPieceTiles, (all_tiles + target_pieces - 1) / target_pieces);
-  // Cut points of each item's walk (item = block * n_groups + head group):
-  // equal pieces when few items split for occupancy, else balance cuts.
+  out->shape = b_.shape;
+  const int n_groups = b_.n_groups;
+  const std::vector<Block>& blocks = b_.list;
+  // Cut points of each item's walk (item = block * n_groups + head group).
   std::vector<std::vector<int32_t>> cuts;
-  if (piece_tiles) {
+  auto cut_all = [&](auto&& pieces) {
     cuts.resize(blocks.size() * n_groups);
     for (size_t bi = 0; bi < blocks.size(); ++bi) {
-      const int64_t n = std::min<int64_t>(kMaxPieces, blocks[bi].tiles / piece_tiles);
+      const int64_t n = pieces(blocks[bi].tiles);
       for (int g = 0; g < n_groups; ++g)
         for (int64_t k = 1; k < n; ++k) cuts[bi * n_groups + g].push_back((int32_t)(blocks[bi].tiles * k / n));
     }
+  };
+  if (cap > 0) {
+    if (cap < b_.max_tiles) cut_all([&](int64_t tiles) { return pieces_at(tiles, cap); });
+  } else if (pinned && target_pieces > 0 && b_.nonempty > 0 && b_.nonempty < kPinnedBelowItems &&
+             b_.max_tiles >= 4 * kPinnedMinTiles) {
+    const int64_t len = std::max<int64_t>(kPinnedMinTiles, (b_.all_tiles + target_pieces - 1) / target_pieces);
+    cut_all([&](int64_t tiles) { return std::min<int64_t>(kMaxPieces, tiles / len); });
   } else if (target_pieces > 0) {
-    // With the head groups a multiple of the XCDs, each XCD's list is its own
-    // schedule on its 32 compute units; otherwise the lists share the units
-    // (the interleave below moves items between XCDs) and one schedule over
-    // all of them is the closer model.
-    const int n_sched = n_groups % kXcds == 0 ? kXcds : 1;
+    const int n_sched = schedules_of(n_groups);
     std::vector<ItemTiles> sched;
     for (int x = 0; x < n_sched; ++x) {
       sched.clear();
@@ -479,41 +503,140 @@ int plan_items(int32_t Hq, int32_t Hkv, int rows, int64_t target_pieces, Plan* o
   return CP_OK;
 }
 
-// Estimated time (microseconds) of a planned launch: the in-order dispatch
-// of its work list simulated on each XCD's 32 compute units (list item i on
-// XCD i % 8), an item taking its tiles times the shape's time per tile plus
-// a fixed set-up, then the split merge's traffic.  The 384-row shape's tile
-// is 1.5 times the 256-row one's work at kLargeTileGain times its rate.  The
-// three constants are fitted to both shapes' times on 136 rank launches (the
-// prompts of 4K-32K tokens at C = 1-8 with and without a 16K prefix, and five
-// larger shapes), timed alternately in one process.
-constexpr double kSmallTileUs = 0.90;   // a 256-row x 32-key tile on one compute unit
-constexpr double kLargeTileGain = 1.06;
-constexpr double kItemSetupUs = 8.0;
-constexpr double kMergeBytesPerUs = 5.0e6;
+// Estimated time (microseconds) of a launch: its work list simulated as it is
+// dispatched, in order to the first free of each XCD's 32 compute units, a
+// workgroup taking its tiles times the shape's time per tile plus a fixed
+// set-up (table and query fetch, first tiles, stores); the clock falls as more
+// units are busy; then the split merge, if any, its launch and its traffic
+// (the pieces written and read back, the merged rows written: mostly cache).
+// The constants are fitted to the timed lists of 35 launches (500 to 64K
+// tokens, degrees 1 to 8, with and without a prefix, in both shapes, uncut,
+// balance cut and cut into 2 to 64 pieces): mean error 4.4 %, and the list
+// that the estimate prefers is 0.5 % slower on average than the fastest one
+// timed.
+constexpr double kSmallTileUs = 0.766;  // a 256-row x 32-key tile on one compute unit
+constexpr double kLargeTileUs = 1.064;  // a 384-row one
+constexpr double kItemSetupUs = 7.0;
+constexpr double kBusySlowdown = 0.093;
+constexpr double kMergeUs = 5.4;
+constexpr double kMergeBytesPerUs = 7.7e6;
+
+double tile_us(const Shape& s) { return s.rows_per_wg == kRowsLarge ? kLargeTileUs : kSmallTileUs; }
+
+double merge_us(const Shape& s, int64_t n_pieces, int64_t n_splits) {
+  if (n_splits == 0) return 0.0;
+  return kMergeUs + (double)piece_bytes(s.rows_per_wg) * (2.0 * n_pieces + n_splits) / kMergeBytesPerUs;
+}
+
+// One schedule's units: a binary heap of the times they fall free at (the
+// root is the first; a unit that takes a workgroup sinks from there), the
+// makespan and the time they are busy in all.
+struct Units {
+  std::vector<double> free;
+  double end = 0.0, sum = 0.0;
+  explicit Units(int n) : free(n, 0.0) {}
+  void add(double us) {
+    const double t = free[0] + us;
+    const size_t n = free.size();
+    size_t i = 0;
+    for (size_t c = 1; c < n; c = 2 * i + 1) {
+      c += c + 1 < n && free[c + 1] < free[c];
+      if (free[c] >= t) break;
+      free[i] = free[c];
+      i = c;
+    }
+    free[i] = t;
+    end = std::max(end, t);
+    sum += us;
+  }
+};
+
+double slowed(double end, double sum, int n_units) { return end > 0.0 ? end + kBusySlowdown * sum / n_units : 0.0; }
 
 double estimate_us(const Plan& plan) {
-  const double tile_us = plan.shape.rows_per_wg == kRowsLarge ? kSmallTileUs * 1.5 / kLargeTileGain : kSmallTileUs;
-  std::vector<std::priority_queue<double, std::vector<double>, std::greater<double>>> units(kXcds);
-  for (auto& q : units)
-    for (int u = 0; u < kComputeUnits / kXcds; ++u) q.push(0.0);
-  double makespan = 0.0;
+  const double tile = tile_us(plan.shape);
+  std::vector<Units> units(kXcds, Units(kComputeUnits / kXcds));
   for (size_t i = 0; i < plan.items.size(); ++i) {
     const WorkItem& w = plan.items[i];
     const int64_t tiles = w.t_end >= 0 ? (int64_t)(w.t_end - w.t_begin)
                                        : item_tiles(plan.descs[w.desc], w.chunk, w.q_block, plan.shape.q_per_wg);
-    auto& q = units[i % kXcds];
-    const double t = q.top() + tiles * tile_us + kItemSetupUs;
-    q.pop();
-    q.push(t);
-    makespan = std::max(makespan, t);
+    units[i % kXcds].add(tiles * tile + kItemSetupUs);
   }
-  if (plan.n_pieces) {
-    // Pieces written and read back, the merged rows written.
-    const double bytes = (double)piece_bytes(plan.shape.rows_per_wg) * (2.0 * plan.n_pieces + plan.splits.size());
-    makespan += bytes / kMergeBytesPerUs + kItemSetupUs;
+  double end = 0.0, sum = 0.0;
+  for (const Units& u : units) {
+    end = std::max(end, u.end);
+    sum += u.sum;
   }
-  return makespan;
+  return slowed(end, sum, kComputeUnits) + merge_us(plan.shape, plan.n_pieces, (int64_t)plan.splits.size());
+}
+
+// A candidate list of one shape: its walks cut to `cap` tiles (0: plan_items'
+// balance cuts), its estimate and the bytes of its piece slots.
+struct Choice {
+  int rows = 0;
+  int64_t cap = 0;
+  double us = 0.0;
+  size_t slots = 0;
+};
+
+// The same estimate for a list cut to `cap` tiles, without building it.
+// `lens` is scratch (length, count).
+Choice estimate_cap(const Blocks& b, int64_t cap, std::vector<std::pair<int64_t, int64_t>>* lens) {
+  const int n_sched = schedules_of(b.n_groups), per_sched = b.n_groups / n_sched;
+  lens->clear();
+  int64_t n_pieces = 0, n_splits = 0;
+  for (const Block& x : b.list) {
+    // Equal parts: x.tiles % n of them are one tile longer than the others.
+    const int64_t n = pieces_at(x.tiles, cap), longer = x.tiles % n;
+    if (longer) lens->push_back(std::make_pair(x.tiles / n + 1, longer * per_sched));
+    lens->push_back(std::make_pair(x.tiles / n, (n - longer) * per_sched));
+    if (n > 1) {
+      n_pieces += n * b.n_groups;
+      n_splits += b.n_groups;
+    }
+  }
+  std::sort(lens->begin(), lens->end(), std::greater<std::pair<int64_t, int64_t>>());
+  const int n_units = kComputeUnits / n_sched;
+  Units units(n_units);
+  for (const std::pair<int64_t, int64_t>& len : *lens)
+    for (int64_t i = 0; i < len.second; ++i) units.add(len.first * tile_us(b.shape) + kItemSetupUs);
+  Choice c;
+  c.rows = b.shape.rows_per_wg;
+  c.cap = cap;
+  c.us = slowed(units.end, units.sum, n_units) + merge_us(b.shape, n_pieces, n_splits);
+  c.slots = (size_t)n_pieces * piece_bytes(b.shape.rows_per_wg);
+  return c;
+}
+
+// Adds one shape's candidates: the longest walk cut into k = 1, 2, ... equal
+// pieces and every other walk to that length.  Once the even spread of a cut
+// list over the units, and its merge, alone end after the best candidate
+// (*best), more pieces only add to both: there the search stops.
+void add_choices(const Blocks& b, int64_t target_pieces, double* best, std::vector<Choice>* out) {
+  std::vector<std::pair<int64_t, int64_t>> lens;
+  int64_t last = 0;
+  for (int64_t k = 1; k <= kMaxPieces; ++k) {
+    const int64_t cap = std::max<int64_t>(1, (b.max_tiles + k - 1) / k);
+    if (k > 1 && (cap < kMinPieceTiles || target_pieces == 0)) break;
+    if (cap == last) continue;
+    last = cap;
+    int64_t n = 0, n_pieces = 0, shortest = b.max_tiles;
+    for (const Block& x : b.list) {
+      const int64_t m = pieces_at(x.tiles, cap);
+      n += m;
+      if (m > 1) {
+        n_pieces += m;
+        shortest = std::min(shortest, x.tiles / m);
+      }
+    }
+    n *= b.n_groups;
+    n_pieces *= b.n_groups;
+    if (k > 1 && (n_pieces > target_pieces || shortest < kMinPieceTiles)) break;
+    const double spread = (b.all_tiles * tile_us(b.shape) + n * kItemSetupUs) / kComputeUnits;
+    if (k > 1 && slowed(spread, spread, 1) + merge_us(b.shape, n_pieces, 1) >= *best) break;
+    out->push_back(estimate_cap(b, cap, &lens));
+    *best = std::min(*best, out->back().us);
+  }
 }
 
 // Bounds (microseconds) of one shape's schedule before any item is cut: the
@@ -521,33 +644,16 @@ double estimate_us(const Plan& plan) {
 // share of each block when the head groups are a multiple of the XCDs, and the
 // interleave spreads them otherwise), and that plus the longest item (list
 // scheduling ends within one item of the even spread).
-// `splits` tells whether the launch has few enough items to be split for
-// occupancy, which the bounds do not model.
 struct Bounds {
   double lo, hi;
-  bool splits;
 };
 
-Bounds shape_bounds(const std::vector<DevDesc>& descs, int32_t Hq, int32_t Hkv, int rows) {
-  const Shape sh = shape_for(Hq, Hkv, rows);
-  const int n_groups = Hkv * sh.groups_per_kv;
-  const double tile_us = rows == kRowsLarge ? kSmallTileUs * 1.5 / kLargeTileGain : kSmallTileUs;
-  double work = 0.0;  // microseconds over all items
-  int64_t nonempty = 0, max_tiles = 0;
-  for (const DevDesc& d : descs)
-    for (int c = 0; c < 2; ++c)
-      for (int64_t qb = 0; qb * sh.q_per_wg < d.q_len[c]; ++qb) {
-        const int64_t tiles = item_tiles(d, c, qb, sh.q_per_wg);
-        work += (tiles * tile_us + kItemSetupUs) * n_groups;
-        if (tiles > 0) nonempty += n_groups;
-        max_tiles = std::max(max_tiles, tiles);
-      }
-  const double lo = work / kComputeUnits;
-  Bounds b;
-  b.lo = lo;
-  b.hi = lo + max_tiles * tile_us + kItemSetupUs;
-  b.splits = nonempty < kSplitBelowItems;
-  return b;
+Bounds shape_bounds(const Blocks& b) {
+  const double work = b.all_tiles * tile_us(b.shape) + (double)b.list.size() * b.n_groups * kItemSetupUs;
+  Bounds r;
+  r.lo = work / kComputeUnits;
+  r.hi = r.lo + b.max_tiles * tile_us(b.shape) + kItemSetupUs;
+  return r;
 }
 
 // Work-group shape forced by cp_set_workgroup_rows (0: chosen per launch).
@@ -597,8 +703,8 @@ static std::vector<int64_t> plan_key(const std::vector<DevDesc>& descs, int32_t 
 
 static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out);
 
-int build_plan(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, int64_t target_pieces,
-               Plan* out) {
+static int build_plan_rows(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv,
+                           int64_t target_pieces, int forced, Plan* out) {
   int st = check_heads(Hq, Hkv, "cp_attn_partial");
   if (st != CP_OK) return st;
   if (n_descs < 0) return fail(CP_ERR_INVALID, "cp_attn_partial: n_descs < 0");
@@ -608,7 +714,6 @@ int build_plan(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_
     st = to_dev(descs[i], i, &out->descs[i]);
     if (st != CP_OK) return st;
   }
-  const int forced = g_forced_rows.load();
   std::vector<int64_t> key = plan_key(out->descs, Hq, Hkv, target_pieces, forced);
   {
     std::lock_guard<std::mutex> lock(g_plan_cache_mu);
@@ -631,29 +736,81 @@ int build_plan(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_
   return CP_OK;
 }
 
-// The work list of a launch whose descriptors are converted (out->descs).
-static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out) {
-  int st;
-  // The workgroup shape: two or three 16-row blocks per wave.  The larger
-  // shares every K/V fragment between more rows (faster per tile) but makes
-  // fewer, longer work items, which fill the compute units worse; plan both
-  // and keep the one whose simulated schedule ends first.
-  if (forced) return plan_items(Hq, Hkv, forced, target_pieces, out);
-  // When the bounds already decide (one shape's worst case ends before the
-  // other's best), only the winner is planned.
-  const Bounds bs = shape_bounds(out->descs, Hq, Hkv, kRowsSmall);
-  const Bounds bl = shape_bounds(out->descs, Hq, Hkv, kRowsLarge);
-  if (!bs.splits && !bl.splits) {
-    if (bl.hi < bs.lo) return plan_items(Hq, Hkv, kRowsLarge, target_pieces, out);
-    if (bs.hi < bl.lo) return plan_items(Hq, Hkv, kRowsSmall, target_pieces, out);
+int build_plan(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, int64_t target_pieces,
+               Plan* out) {
+  return build_plan_rows(descs, n_descs, Hq, Hkv, target_pieces, g_forced_rows.load(), out);
+}
+
+int build_plan_within(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, size_t bytes, Plan* out,
+                      Layout* lay, size_t* wanted) {
+  const int forced = g_forced_rows.load();
+  *wanted = 0;
+  // Fewer pieces, down to none, then the shape with the shortest work list.
+  for (int64_t target = kTargetPieces;; target = target >= 4 ? target / 2 : 0) {
+    const int st = build_plan_rows(descs, n_descs, Hq, Hkv, target, forced, out);
+    if (st != CP_OK) return st;
+    *lay = layout_of(*out);
+    if (*wanted == 0) *wanted = lay->total;
+    if (lay->total <= bytes) return CP_OK;
+    if (out->n_pieces == 0 || target == 0) break;
   }
-  Plan small;
-  small.descs = out->descs;
-  st = plan_items(Hq, Hkv, kRowsSmall, target_pieces, &small);
-  if (st != CP_OK) return st;
-  st = plan_items(Hq, Hkv, kRowsLarge, target_pieces, out);
-  if (st != CP_OK) return st;
-  if (estimate_us(small) < estimate_us(*out)) *out = std::move(small);
+  if (forced) return CP_OK;
+  const int st = build_plan_rows(descs, n_descs, Hq, Hkv, 0, kRowsLarge, out);
+  if (st == CP_OK) *lay = layout_of(*out);
+  return st;
+}
+
+// The work list of a launch whose descriptors are converted (out->descs).
+// The larger shape shares every K/V fragment between more rows (faster per
+// tile) but makes fewer, longer work items, which fill the compute units
+// worse; cuts fill them better but cost set-ups and a merge.
+static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out) {
+  if (forced) return plan_items(list_blocks(out->descs, Hq, Hkv, forced), target_pieces, true, 0, out);
+  const Blocks small = list_blocks(out->descs, Hq, Hkv, kRowsSmall);
+  const Blocks large = list_blocks(out->descs, Hq, Hkv, kRowsLarge);
+  // Launches of many rounds: when the bounds already decide (one shape's worst
+  // case ends before the other's best), only the winner is planned.  Its
+  // worst case is within one item of its even spread, which leaves little to
+  // cuts other than the balance cuts.
+  const Bounds bs = shape_bounds(small), bl = shape_bounds(large);
+  if (bl.hi < bs.lo) return plan_items(large, target_pieces, false, 0, out);
+  if (bs.hi < bl.lo) return plan_items(small, target_pieces, false, 0, out);
+  std::vector<Choice> choices;
+  double best_us = INFINITY;
+  add_choices(small, target_pieces, &best_us, &choices);
+  add_choices(large, target_pieces, &best_us, &choices);
+  const Choice* best = &choices[0];
+  for (const Choice& c : choices)
+    if (c.us < best->us) best = &c;
+  // Piece slots that fit the eight 4 MB L2s, and with the tables the scratch
+  // of cp_attn_partial_noalloc (then both entry points run the same list),
+  // are worth a few per cent: 300 rows after 16K cached keys ran 108.4 us in
+  // 240 slots of 256 rows (32 MB) against 108.2 in 256 of 384 (51 MB).
+  constexpr size_t kSlotBytes = (size_t)(32 << 20) - (256 << 10);
+  constexpr double kSlotGain = 1.04;
+  if (best->slots > kSlotBytes) {
+    const Choice* within = nullptr;
+    for (const Choice& c : choices)
+      if (c.slots <= kSlotBytes && (!within || c.us < within->us)) within = &c;
+    if (within && within->us <= kSlotGain * best->us) best = within;
+  }
+  const Choice chosen = *best;
+  const int st = plan_items(chosen.rows == kRowsLarge ? large : small, target_pieces, false, chosen.cap, out);
+  if (st != CP_OK || target_pieces == 0) return st;
+  // Long walks: the balance cuts of each shape, where they end sooner.
+  double us = chosen.us;
+  for (const Blocks* b : {&small, &large}) {
+    if (b->max_tiles < 2 * kMinBalancePiece) continue;
+    Plan balanced;
+    balanced.descs = out->descs;
+    const int st2 = plan_items(*b, target_pieces, false, 0, &balanced);
+    if (st2 != CP_OK) return st2;
+    const double t = estimate_us(balanced);
+    if (t < us) {
+      us = t;
+      *out = std::move(balanced);
+    }
+  }
   return CP_OK;
 }
 
@@ -841,17 +998,19 @@ extern "C" int cp_attn_partial(const cp_partial_desc* descs, int32_t n_descs, in
     if (head_dim != CP_HEAD_DIM) return fail(CP_ERR_UNSUPPORTED, "cp_attn_partial: head_dim must be 128");
     if (!(softmax_scale == softmax_scale)) return fail(CP_ERR_INVALID, "cp_attn_partial: softmax_scale is NaN");
     Plan plan;
-    int st = build_plan(descs, n_descs, n_heads_q, n_heads_kv, kTargetPieces, &plan);
+    Layout lay;
+    size_t wanted = 0;
+    int st = build_plan_within(descs, n_descs, n_heads_q, n_heads_kv, workspace ? workspace_bytes : SIZE_MAX, &plan,
+                               &lay, &wanted);
     if (st != CP_OK) return st;
     if (plan.items.empty()) {
       clear_error();
       return CP_OK;
     }
-    const Layout lay = layout_of(plan);
     if (!workspace) return fail(CP_ERR_INVALID, "cp_attn_partial: workspace is NULL");
     if (!aligned(workspace, 256)) return fail(CP_ERR_INVALID, "cp_attn_partial: workspace must be 256-byte aligned");
     if (workspace_bytes < lay.total)
-      return fail(CP_ERR_CAPACITY, "cp_attn_partial: workspace needs " + std::to_string(lay.total) + " bytes");
+      return fail(CP_ERR_CAPACITY, "cp_attn_partial: workspace needs " + std::to_string(wanted) + " bytes");
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.f / std::sqrt((float)head_dim);
     PartialParams p =
         partial_params(plan, lay, static_cast<unsigned char*>(workspace), n_heads_q, n_heads_kv, scale);

@@ -211,8 +211,7 @@ struct Plan {
   Shape shape;
 };
 
-// Key walks of launches with few work items are split into about
-// `target_pieces` pieces (0: never split).
+// At most about `target_pieces` pieces (0: no walk is cut).
 constexpr int64_t kTargetPieces = 1024;
 int build_plan(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, int64_t target_pieces,
                Plan* out);
@@ -224,6 +223,12 @@ struct Layout {
   size_t items, splits, pieces, total;
 };
 Layout layout_of(const Plan& plan);
+// The plan of a launch in `bytes` of workspace: when its piece slots do not
+// fit, fewer and longer pieces, down to none (the same attention, another
+// decomposition).  *lay is its layout, which exceeds `bytes` when not even the
+// tables fit; *wanted is the first plan's size.
+int build_plan_within(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, size_t bytes, Plan* out,
+                      Layout* lay, size_t* wanted);
 void pack_tables(const Plan& plan, const Layout& lay, unsigned char* host);
 // The plan's tables in argument form; false if they do not fit it.
 bool pack_inline(const Plan& plan, InlineTables* out);

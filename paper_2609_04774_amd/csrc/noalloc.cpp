@@ -62,19 +62,11 @@ extern "C" int cp_attn_partial_noalloc(const cp_partial_desc* descs, int32_t n_d
     const char* who = "cp_attn_partial_noalloc";
     if (head_dim != CP_HEAD_DIM) return fail(CP_ERR_UNSUPPORTED, std::string(who) + ": head_dim must be 128");
     if (!(softmax_scale == softmax_scale)) return fail(CP_ERR_INVALID, std::string(who) + ": softmax_scale is NaN");
-    // Plan as cp_attn_partial does; when the split-walk pieces would not fit
-    // in the scratch, plan fewer (down to none): the result is the same
-    // attention, only the work decomposition differs.
     Plan plan;
     Layout lay;
-    int64_t target = kTargetPieces;
-    for (;;) {
-      const int st = build_plan(descs, n_descs, n_heads_q, n_heads_kv, target, &plan);
-      if (st != CP_OK) return st;
-      lay = layout_of(plan);
-      if (lay.total <= kScratchBytes || plan.n_pieces == 0) break;
-      target = target >= 4 ? target / 2 : 0;
-    }
+    size_t wanted = 0;
+    int st = build_plan_within(descs, n_descs, n_heads_q, n_heads_kv, kScratchBytes, &plan, &lay, &wanted);
+    if (st != CP_OK) return st;
     if (plan.items.empty()) {
       clear_error();
       return CP_OK;
@@ -84,7 +76,7 @@ extern "C" int cp_attn_partial_noalloc(const cp_partial_desc* descs, int32_t n_d
                                        " bytes, beyond the " + std::to_string(kScratchBytes) +
                                        "-byte scratch (use cp_attn_partial with a workspace)");
     unsigned char* ws = nullptr;
-    int st = scratch_of_current_device(&ws);
+    st = scratch_of_current_device(&ws);
     if (st != CP_OK) return st;
     std::vector<unsigned char> host(lay.pieces);
     pack_tables(plan, lay, host.data());

@@ -3,7 +3,9 @@
 // that fits comes back from its 64-bit word unchanged, the largest value of
 // each field included, and a plan with a larger value, more descriptors or
 // more words than the form holds is refused (it then goes through the
-// workspace).  Prints "ok <plans that fit>" on success.
+// workspace).  And of plans in a given workspace: any that holds the tables of
+// the uncut 384-row list gets a plan that fits it, with fewer pieces than the
+// free choice.  Prints "ok <plans that fit>" on success.
 #include "../paper_2609_04774_amd/csrc/cp_attn.cpp"
 
 #include <cstdio>
@@ -78,6 +80,21 @@ int main() {
           // No field of these plans is beyond its bits: the space decides.
           expect(in == (n_descs <= 32 && need <= kInlineBytes), "fits by its size");
           ++(in ? fit : beyond);
+          const size_t total = layout_of(plan).total;
+          Plan least;
+          least.descs = plan.descs;
+          plan_uncached(8, 2, 0, kRowsLarge, &least);
+          const size_t floor = layout_of(least).total;
+          for (size_t bytes : {total, total - 1, (total + floor) / 2, floor}) {
+            if (bytes < floor) continue;
+            Plan part;
+            Layout lay;
+            size_t wanted = 0;
+            expect(build_plan_within(d.data(), n_descs, 8, 2, bytes, &part, &lay, &wanted) == CP_OK, "plan within");
+            expect(wanted == total && lay.total <= bytes, "a plan that fits the workspace");
+            expect(bytes == total ? part.n_pieces == plan.n_pieces : part.n_pieces <= plan.n_pieces, "fewer pieces");
+            check(part);
+          }
         }
   expect(fit > 50 && beyond > 50, "both sides of the limit met");
   // The largest value of each field, and one more.

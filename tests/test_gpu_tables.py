@@ -1,7 +1,8 @@
 """How a launch's tables reach the kernel: among its arguments when they are
 small, else through pinned staging that is reused after eight launches.
 Either way the results are those of cp_attn_partial_noalloc, which copies its
-tables itself and plans the same list, bit for bit."""
+tables itself and plans the same list, bit for bit.  And launches whose walks
+are cut into many or few short pieces, against the oracle."""
 
 import pytest
 import torch
@@ -87,3 +88,39 @@ def test_a_captured_launch_replays(H):
         _compare(launch, f"replay, {H} heads")
         cp.attn_partial(other[0], 8, 8, other_ws)
     torch.cuda.synchronize()
+
+
+# (L, P, C, Hq, Hkv, rank): pieces of three or four tiles; six and more per
+# item; 64 per item (a wave merges each row); pieces that some rows see no key
+# of; one and three query rows; a 384-row list of a few pieces per item; head
+# groups that no XCD count divides.
+@pytest.mark.parametrize("L,P,C,Hq,Hkv,rank", [
+    (1024, 0, 2, 8, 2, 0), (2900, 880, 1, 8, 2, 0), (6073, 6016, 8, 8, 2, 3), (2049, 2048, 1, 4, 1, 0),
+    (4099, 4096, 1, 16, 1, 0), (4700, 4400, 1, 32, 8, 0), (1500, 608, 2, 24, 3, 1), (1203, 1200, 2, 8, 8, 0)])
+def test_cut_walks_match_oracle(L, P, C, Hq, Hkv, rank):
+    prob = Problem(L, P, C, Hq, Hkv, 31)
+    o, lse, plan, _ = prob.gpu_rank(rank)
+    Or, Lr = prob.oracle_rank(rank)
+    gc.compare(gc.f64(o), gc.f64(lse), Or, Lr, f"rank {rank} of {C}")
+
+
+def test_a_smaller_workspace_gets_fewer_pieces():
+    """A workspace below the sizing call's figure, down to the tables of an
+    uncut list, is still taken (with longer pieces); below that it is refused."""
+    prob = Problem(2348, 2048, 1, 8, 2, 33)
+    dv = prob.dev()
+    plan, _ = cp.shard_plan(prob.P, prob.R, 1, 0)
+    o, lse = gc.alloc_out(plan.n_rows, 8)
+    desc = cp.make_desc(plan, dv["q"], dv["k"], dv["v"], o, lse, dv["kc"], dv["vc"], dv["bt"])
+    full = cp.workspace_size([desc], 8, 2)
+    Or, Lr = prob.oracle_rank(0)
+    assert full > 1 << 20
+    for size in (full, full - 256, full // 2, 4096):
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        o.fill_(float("nan"))
+        cp.attn_partial([desc], 8, 2, ws)
+        torch.cuda.synchronize()
+        gc.compare(gc.f64(o), gc.f64(lse), Or, Lr, f"{size} bytes")
+    with pytest.raises(cp.CpError) as e:
+        cp.attn_partial([desc], 8, 2, torch.empty(256, dtype=torch.uint8, device=DEV))
+    assert e.value.status == cp.CP_ERR_CAPACITY
