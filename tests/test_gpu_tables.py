@@ -2,7 +2,8 @@
 small, else through pinned staging that is reused after eight launches.
 Either way the results are those of cp_attn_partial_noalloc, which copies its
 tables itself and plans the same list, bit for bit.  And launches whose walks
-are cut into many or few short pieces, against the oracle."""
+are cut into many or few short pieces, against the oracle; and merges of every
+partial count."""
 
 import pytest
 import torch
@@ -124,3 +125,30 @@ def test_a_smaller_workspace_gets_fewer_pieces():
     with pytest.raises(cp.CpError) as e:
         cp.attn_partial([desc], 8, 2, torch.empty(256, dtype=torch.uint8, device=DEV))
     assert e.value.status == cp.CP_ERR_CAPACITY
+
+
+@pytest.mark.parametrize("n", range(1, 17))
+def test_merge_of_every_partial_count(n):
+    """Each partial count has its own kernel up to eight; 31 and 33 rows end a
+    block and a two-row group short.  fp32: weights within 2^-21 (expf, one
+    division) and n products, |O| below 6: 1e-5; bf16: half an ulp more."""
+    g = torch.Generator().manual_seed(50 + n)
+    for n_tok, H in ((31, 1), (11, 3), (100, 5)):
+        o = [torch.randn(n_tok, H, 128, generator=g) for _ in range(n)]
+        lse = [torch.randn(n_tok, H, generator=g) * 4 for _ in range(n)]
+        for i in range(n):
+            lse[i][torch.rand(n_tok, H, generator=g) < 0.2] = float("-inf")
+        w = torch.stack(lse).double()
+        L = torch.logsumexp(w, 0)
+        ref = sum(torch.nan_to_num((w[i] - L).exp())[..., None] * o[i].double() for i in range(n))
+        od, ld = [x.to(DEV) for x in o], [x.to(DEV) for x in lse]
+        O, Ob = torch.empty(n_tok, H, 128, device=DEV), torch.empty(n_tok, H, 128, dtype=torch.bfloat16, device=DEV)
+        Lo = torch.empty(n_tok, H, device=DEV)
+        cp.attn_merge(od, ld, O, Lo)
+        cp.attn_merge(od, ld, Ob)
+        torch.cuda.synchronize()
+        live = torch.isfinite(L)
+        assert torch.equal(torch.isfinite(Lo.cpu()), live)
+        assert float((Lo.cpu().double() - L)[live].abs().max()) < 5e-6
+        assert float((O.cpu().double() - ref).abs().max()) < 1e-5
+        assert bool(((Ob.cpu().double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all())
