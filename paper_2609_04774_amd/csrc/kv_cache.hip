@@ -9,11 +9,26 @@
 //  * Paged gather (Sec. 2.2, 7.1, 7.2): positions of a request read back out
 //    of the paged cache into contiguous rows.
 //
-// A workgroup takes 4 rows, one wave per row; each lane moves
-// 16-byte pieces with plain vector loads and stores, so a row's bytes are
-// read and written in fully coalesced 1 KiB wavefront accesses.  Row indices are derived in
-// closed form from the zigzag plans; no index table is read except the
-// block table.
+// A row (of K and of V, where both move alike) is copied by 16, 32 or 64 lanes,
+// the fewest that hold a narrow row's 16-byte pieces one each, with up to four
+// pieces per lane and tensor loaded before any is stored, so that a row's bytes
+// are read and written in fully coalesced accesses and no lane idles on the
+// rows of one or two KV heads (256 and 512 bytes).  Row indices are derived in
+// closed form from the zigzag plans; no index table is read except the block
+// table.
+//
+// Bound by HBM.  Against one wave per row, K's row before V's: 65536 rows of
+// one KV head gathered 20.2 -> 12.0 us, of two 25.2 -> 22.9, re-sharded 28.7 ->
+// 20.7; a 128K request of eight re-sharded (two tensors at once) 180 -> 170 us
+// (6.3 TB/s).
+//
+// Stores carry non-temporal hints, and so do loads except the write-back's up
+// to the size of the 256 MB Infinity Cache, which may hold the rows its caller
+// has just computed: a rank's 16384 rows of the 128K prompt take 20.7 us (6.5
+// TB/s) whether a cache holds them or not, with streaming loads 24-27, and with
+// plain stores 28 when none does.  Beyond that size, and for the gather and the
+// re-shard, streaming loads are the faster: 131000 rows written back 200
+// against 206 us, a 48K prefix gathered 69 against 73.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -23,27 +38,45 @@ namespace cpattn {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
-constexpr int kRowsPerGroup = 4;  // rows copied by one workgroup, one wave per row
+constexpr int64_t kInfinityCacheBytes = 256 << 20;
+constexpr int kPieces = 4;  // 16-byte pieces of a row and tensor in flight per lane
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// One wave copies one row: lane l moves 16-byte pieces l, l+64, ...; four
-// loads are in flight before their stores.
-__device__ __forceinline__ void copy_row(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
-                                         int64_t row_bytes, int lane) {
+// kLanes lanes copy one row of kSets tensors: lane l moves 16-byte pieces l,
+// l + kLanes, ...  A null source writes zeros.
+// kStream: loads with the non-temporal hint.
+template <int kLanes, int kSets, bool kStream = true>
+__device__ __forceinline__ void copy_rows(const unsigned char* const (&src)[kSets], unsigned char* const (&dst)[kSets],
+                                          int64_t row_bytes, int lane) {
   const int64_t n = row_bytes >> 4;
-  const u32x4* s = reinterpret_cast<const u32x4*>(src);
-  u32x4* d = reinterpret_cast<u32x4*>(dst);
-  int64_t i = lane;
-  for (; i + 192 < n; i += 256) {
-    const u32x4 a = s[i], b = s[i + 64], c = s[i + 128], e = s[i + 192];
-    d[i] = a;
-    d[i + 64] = b;
-    d[i + 128] = c;
-    d[i + 192] = e;
+  for (int64_t base = 0; base < n; base += kPieces * kLanes) {
+    u32x4 v[kPieces][kSets];
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+      const int64_t i = base + lane + kLanes * k;
+#pragma unroll
+      for (int s = 0; s < kSets; ++s) {
+        v[k][s] = u32x4{0u, 0u, 0u, 0u};
+        if (i >= n || !src[s]) continue;
+        const u32x4* from = reinterpret_cast<const u32x4*>(src[s]) + i;
+        v[k][s] = kStream ? __builtin_nontemporal_load(from) : *from;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+      const int64_t i = base + lane + kLanes * k;
+#pragma unroll
+      for (int s = 0; s < kSets; ++s)
+        if (i < n) __builtin_nontemporal_store(v[k][s], reinterpret_cast<u32x4*>(dst[s]) + i);
+    }
   }
-  for (; i < n; i += 64) d[i] = s[i];
+}
+
+// This thread's row of the launch.
+template <int kLanes>
+__device__ __forceinline__ int64_t row_index() {
+  return (int64_t)blockIdx.x * (kThreads / kLanes) + threadIdx.x / kLanes;
 }
 
 // Global position of a rank's local row t: chunk 0's rows, then chunk 1's.
@@ -51,39 +84,16 @@ __device__ __forceinline__ int64_t row_position(const int64_t (&q_begin)[2], con
   return t < q_len[0] ? q_begin[0] + t : q_begin[1] + (t - q_len[0]);
 }
 
+template <int kLanes, bool kStream>
 __global__ __launch_bounds__(kThreads) void kv_writeback_kernel(WritebackParams p) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = wave; k < kRowsPerGroup; k += kWaves) {
-    const int64_t t = (int64_t)blockIdx.x * kRowsPerGroup + k;
-    if (t >= p.n_rows) break;
-    const int64_t pos = row_position(p.q_begin, p.q_len, t);
-    const int64_t blk = p.block_table[pos / kBlockTokens];
-    if (blk < 0 || blk >= p.n_blocks) continue;  // outside the cache: nothing is written
-    const int64_t dst = (blk * kBlockTokens + pos % kBlockTokens) * p.row_bytes;
-    copy_row(p.k_rows + t * p.row_bytes, p.k_cache + dst, p.row_bytes, lane);
-    copy_row(p.v_rows + t * p.row_bytes, p.v_cache + dst, p.row_bytes, lane);
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void repartition_kernel(RepartitionParams p) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = wave; k < kRowsPerGroup; k += kWaves) {
-    const int64_t t = (int64_t)blockIdx.x * kRowsPerGroup + k;
-    if (t >= p.n_rows) break;
-    // Source rank of the row's global position: suffix chunk c at the source
-    // degree belongs to rank c (c < C) or 2C-1-c; its local row follows that
-    // rank's first chunk when c is its second chunk.
-    const int64_t i = row_position(p.dst_q_begin, p.dst_q_len, t) - p.P;
-    const int64_t c = i / p.s_src;
-    const int64_t C = p.C_src;
-    const int64_t r = c < C ? c : 2 * C - 1 - c;
-    int64_t local = i - c * p.s_src;
-    if (c != r) {
-      const int64_t first = p.R - r * p.s_src;  // rows of rank r's first chunk
-      local += first < 0 ? 0 : (first > p.s_src ? p.s_src : first);
-    }
-    copy_row(p.src[r] + local * p.row_bytes, p.dst + t * p.row_bytes, p.row_bytes, lane);
-  }
+  const int64_t t = row_index<kLanes>();
+  if (t >= p.n_rows) return;
+  const int64_t pos = row_position(p.q_begin, p.q_len, t);
+  const int64_t blk = p.block_table[pos / kBlockTokens];
+  if (blk < 0 || blk >= p.n_blocks) return;  // outside the cache: nothing is written
+  const int64_t dst = (blk * kBlockTokens + pos % kBlockTokens) * p.row_bytes;
+  copy_rows<kLanes, 2, kStream>({p.k_rows + t * p.row_bytes, p.v_rows + t * p.row_bytes},
+                                {p.k_cache + dst, p.v_cache + dst}, p.row_bytes, threadIdx.x % kLanes);
 }
 
 // Where suffix index i sits at degree C with chunk length s: the rank holding
@@ -104,104 +114,89 @@ __device__ __forceinline__ RankRow rank_row(int64_t i, int64_t C, int64_t s, int
   return RankRow{r, local};
 }
 
-// One wave per (set, suffix index): the row moves from its source rank to its
-// destination rank.
+// One destination rank: each of its rows fetched from where it sits at the
+// source degree.
+template <int kLanes>
+__global__ __launch_bounds__(kThreads) void repartition_kernel(RepartitionParams p) {
+  const int64_t t = row_index<kLanes>();
+  if (t >= p.n_rows) return;
+  const RankRow from = rank_row(row_position(p.dst_q_begin, p.dst_q_len, t) - p.P, p.C_src, p.s_src, p.R);
+  copy_rows<kLanes, 1>({p.src[from.rank] + from.row * p.row_bytes}, {p.dst + t * p.row_bytes}, p.row_bytes,
+                       threadIdx.x % kLanes);
+}
+
+// Every row of the suffix from its source rank to its destination rank, in
+// kSets row sets at once.
+template <int kLanes, int kSets>
 __global__ __launch_bounds__(kThreads) void repartition_all_kernel(RepartitionAllParams p) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = wave; k < kRowsPerGroup; k += kWaves) {
-    const int64_t t = (int64_t)blockIdx.x * kRowsPerGroup + k;
-    if (t >= p.n_sets * p.R) break;
-    const int set = t >= p.R ? 1 : 0;
-    const int64_t i = t - set * p.R;
-    const RankRow from = rank_row(i, p.C_src, p.s_src, p.R);
-    const RankRow to = rank_row(i, p.C_dst, p.s_dst, p.R);
-    copy_row(p.src[set][from.rank] + from.row * p.row_bytes, p.dst[set][to.rank] + to.row * p.row_bytes,
-             p.row_bytes, lane);
+  const int64_t i = row_index<kLanes>();
+  if (i >= p.R) return;
+  const RankRow from = rank_row(i, p.C_src, p.s_src, p.R);
+  const RankRow to = rank_row(i, p.C_dst, p.s_dst, p.R);
+  const unsigned char* src[kSets];
+  unsigned char* dst[kSets];
+#pragma unroll
+  for (int s = 0; s < kSets; ++s) {
+    src[s] = p.src[s][from.rank] + from.row * p.row_bytes;
+    dst[s] = p.dst[s][to.rank] + to.row * p.row_bytes;
   }
+  copy_rows<kLanes, kSets>(src, dst, p.row_bytes, threadIdx.x % kLanes);
 }
 
-// One wave gathers one row of K and one of V out of the paged cache: per
-// round, up to four 16-byte pieces of each (lane l takes pieces l, l+64, ...)
-// are loaded before any is stored, with non-temporal hints (every byte is
-// moved once).  A NULL source (a block-table entry outside the cache) writes
-// zeros.
-__device__ __forceinline__ void gather_row_pair(const unsigned char* ks, const unsigned char* vs,
-                                                unsigned char* kd, unsigned char* vd, int64_t row_bytes,
-                                                int lane) {
-  const int64_t n = row_bytes >> 4;
-  for (int64_t base = 0; base < n; base += 4 * 64) {
-    u32x4 kv[4], vv[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t i = base + lane + 64 * k;
-      kv[k] = vv[k] = u32x4{0u, 0u, 0u, 0u};
-      if (i < n && ks) {
-        kv[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ks) + i);
-        vv[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vs) + i);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t i = base + lane + 64 * k;
-      if (i < n) {
-        __builtin_nontemporal_store(kv[k], reinterpret_cast<u32x4*>(kd) + i);
-        __builtin_nontemporal_store(vv[k], reinterpret_cast<u32x4*>(vd) + i);
-      }
-    }
-  }
-}
-
+// A block-table entry outside the cache gives zero rows.
+template <int kLanes>
 __global__ __launch_bounds__(kThreads) void kv_gather_kernel(GatherParams p) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = wave; k < kRowsPerGroup; k += kWaves) {
-    const int64_t t = (int64_t)blockIdx.x * kRowsPerGroup + k;
-    if (t >= p.n_rows) break;
-    const int64_t pos = p.pos_begin + t;
-    const int64_t blk = p.block_table[pos / kBlockTokens];
-    const bool inside = blk >= 0 && blk < p.n_blocks;
-    const int64_t src = (blk * kBlockTokens + pos % kBlockTokens) * p.row_bytes;
-    gather_row_pair(inside ? p.k_cache + src : nullptr, inside ? p.v_cache + src : nullptr,
-                    p.k_rows + t * p.row_bytes, p.v_rows + t * p.row_bytes, p.row_bytes, lane);
-  }
+  const int64_t t = row_index<kLanes>();
+  if (t >= p.n_rows) return;
+  const int64_t pos = p.pos_begin + t;
+  const int64_t blk = p.block_table[pos / kBlockTokens];
+  const bool inside = blk >= 0 && blk < p.n_blocks;
+  const int64_t src = (blk * kBlockTokens + pos % kBlockTokens) * p.row_bytes;
+  copy_rows<kLanes, 2>({inside ? p.k_cache + src : nullptr, inside ? p.v_cache + src : nullptr},
+                       {p.k_rows + t * p.row_bytes, p.v_rows + t * p.row_bytes}, p.row_bytes, threadIdx.x % kLanes);
+}
+
+// Launches the kernel of the fewest lanes that hold a row's pieces one each.
+template <class Params>
+int launch_rows(void (*k16)(Params), void (*k32)(Params), void (*k64)(Params), const Params& p, int64_t rows,
+                const char* who, void* stream) {
+  if (rows == 0) return CP_OK;
+  const int64_t pieces = p.row_bytes >> 4;
+  const int lanes = pieces <= 16 ? 16 : pieces <= 32 ? 32 : 64;
+  const int64_t per_block = kThreads / lanes;
+  hipLaunchKernelGGL(lanes == 16 ? k16 : lanes == 32 ? k32 : k64, dim3((unsigned)((rows + per_block - 1) / per_block)),
+                     dim3(kThreads), 0, (hipStream_t)stream, p);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string(who) + " launch: " + hipGetErrorString(e));
+  return CP_OK;
 }
 
 }  // namespace
 
 int launch_repartition_all(const RepartitionAllParams& p, void* stream) {
-  const int64_t rows = p.n_sets * p.R;
-  if (rows == 0) return CP_OK;
-  const int64_t groups = (rows + kRowsPerGroup - 1) / kRowsPerGroup;
-  hipLaunchKernelGGL(repartition_all_kernel, dim3((unsigned)groups), dim3(kThreads), 0, (hipStream_t)stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("cp_repartition_all launch: ") + hipGetErrorString(e));
-  return CP_OK;
+  if (p.n_sets == 2)
+    return launch_rows(repartition_all_kernel<16, 2>, repartition_all_kernel<32, 2>, repartition_all_kernel<64, 2>, p,
+                       p.R, "cp_repartition_all", stream);
+  return launch_rows(repartition_all_kernel<16, 1>, repartition_all_kernel<32, 1>, repartition_all_kernel<64, 1>, p,
+                     p.R, "cp_repartition_all", stream);
 }
 
 int launch_gather(const GatherParams& p, void* stream) {
-  if (p.n_rows == 0) return CP_OK;
-  const int64_t groups = (p.n_rows + kRowsPerGroup - 1) / kRowsPerGroup;
-  hipLaunchKernelGGL(kv_gather_kernel, dim3((unsigned)groups), dim3(kThreads), 0, (hipStream_t)stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("cp_kv_gather launch: ") + hipGetErrorString(e));
-  return CP_OK;
+  return launch_rows(kv_gather_kernel<16>, kv_gather_kernel<32>, kv_gather_kernel<64>, p, p.n_rows, "cp_kv_gather",
+                     stream);
 }
 
 int launch_writeback(const WritebackParams& p, void* stream) {
-  if (p.n_rows == 0) return CP_OK;
-  const int64_t groups = (p.n_rows + kRowsPerGroup - 1) / kRowsPerGroup;
-  hipLaunchKernelGGL(kv_writeback_kernel, dim3((unsigned)groups), dim3(kThreads), 0, (hipStream_t)stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("cp_kv_writeback launch: ") + hipGetErrorString(e));
-  return CP_OK;
+  if (2 * p.n_rows * p.row_bytes > kInfinityCacheBytes)
+    return launch_rows(kv_writeback_kernel<16, true>, kv_writeback_kernel<32, true>, kv_writeback_kernel<64, true>, p,
+                       p.n_rows, "cp_kv_writeback", stream);
+  return launch_rows(kv_writeback_kernel<16, false>, kv_writeback_kernel<32, false>, kv_writeback_kernel<64, false>, p,
+                     p.n_rows, "cp_kv_writeback", stream);
 }
 
 int launch_repartition(const RepartitionParams& p, void* stream) {
-  if (p.n_rows == 0) return CP_OK;
-  const int64_t groups = (p.n_rows + kRowsPerGroup - 1) / kRowsPerGroup;
-  hipLaunchKernelGGL(repartition_kernel, dim3((unsigned)groups), dim3(kThreads), 0, (hipStream_t)stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("cp_repartition launch: ") + hipGetErrorString(e));
-  return CP_OK;
+  return launch_rows(repartition_kernel<16>, repartition_kernel<32>, repartition_kernel<64>, p, p.n_rows,
+                     "cp_repartition", stream);
 }
 
 }  // namespace cpattn

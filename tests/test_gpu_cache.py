@@ -255,3 +255,57 @@ def test_gather_full_size_round_trip():
     idx = pre.block_table.long()[pos // B] * B + pos % B
     assert torch.equal(k, pre.k_cache.reshape(-1, w.Hkv, w.D)[idx])
     assert torch.equal(v, pre.v_cache.reshape(-1, w.Hkv, w.D)[idx])
+
+
+# 16-byte pieces per row: 1, 15, 16, 17, 32, 33, 64, 65 and 272 -- either side of
+# the 16, 32 and 64 lanes a row can take, and of the 256 pieces one pass of 64
+# lanes moves.
+@pytest.mark.parametrize("Hkv,D", [(1, 8), (1, 120), (1, 128), (1, 136), (2, 128), (3, 88), (4, 128), (5, 104),
+                                   (16, 136)])
+def test_every_row_width_moves_whole(Hkv, D):
+    g = torch.Generator().manual_seed(91)
+    P, R, C = 32, 203, 2
+    nb = -(-(P + R) // 16) + 2
+    table = torch.randperm(nb, generator=g)[: nb - 2].to(torch.int32)
+    k, v = (torch.randn(R, Hkv, D, generator=g).to(torch.bfloat16) for _ in range(2))
+    kc = torch.zeros(nb, 16, Hkv, D, dtype=torch.bfloat16, device=DEV)
+    vc = torch.zeros_like(kc)
+    src = [[], []]
+    for r in range(C):
+        plan, rows = cp.shard_plan(P, R, C, r)
+        idx = torch.as_tensor(rows - P)
+        src[0].append(k[idx].to(DEV))
+        src[1].append(v[idx].to(DEV))
+        cp.kv_writeback(plan, src[0][r], src[1][r], kc, vc, table.to(DEV))
+    pos = torch.arange(P, P + R)
+    where = table[pos // 16].long() * 16 + pos % 16
+    assert torch.equal(kc.cpu().flatten(0, 1)[where], k) and torch.equal(vc.cpu().flatten(0, 1)[where], v)
+    ko, vo = (torch.zeros(R - 5, Hkv, D, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    cp.kv_gather(kc, vc, table.to(DEV), P + 5, ko, vo)
+    assert torch.equal(ko.cpu(), k[5:]) and torch.equal(vo.cpu(), v[5:])
+    dst = [[torch.zeros(cp.shard_plan(P, R, 3, r)[0].n_rows, Hkv, D, dtype=torch.bfloat16, device=DEV)
+            for r in range(3)] for _ in range(2)]
+    cp.repartition_all(P, R, src, dst)
+    one = torch.zeros_like(dst[0][1])
+    cp.repartition(P, R, src[0], 3, 1, one)
+    single = [torch.zeros_like(t) for t in dst[1]]
+    cp.repartition_all(P, R, src[1:], [single])
+    for r in range(3):
+        idx = torch.as_tensor(cp.shard_plan(P, R, 3, r)[1] - P)
+        assert torch.equal(dst[0][r].cpu(), k[idx]) and torch.equal(dst[1][r].cpu(), v[idx])
+        assert torch.equal(single[r].cpu(), v[idx])
+    assert torch.equal(one, dst[0][1])
+
+
+@pytest.mark.parametrize("R", [65536, 65537])
+def test_writeback_on_both_sides_of_the_infinity_cache(R):
+    """256 MB of rows, and just more (streaming loads)."""
+    k, v = (torch.randint(-2 ** 15, 2 ** 15, (R, 8, 128), dtype=torch.int16, device=DEV).view(torch.bfloat16)
+            for _ in range(2))
+    table = torch.randperm(R // 16 + 1, device=DEV).to(torch.int32)
+    kc, vc = (torch.zeros(R // 16 + 1, 16, 8, 128, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    cp.kv_writeback(cp.shard_plan(0, R, 1, 0, with_rows=False)[0], k, v, kc, vc, table)
+    ko, vo = torch.zeros_like(k), torch.zeros_like(v)
+    cp.kv_gather(kc, vc, table, 0, ko, vo)
+    for a, b in ((k, ko), (v, vo)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
