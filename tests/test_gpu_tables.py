@@ -31,11 +31,12 @@ def _compare(launch, what):
         assert torch.equal(outs[i][0], outs[n + i][0]) and torch.equal(outs[i][1], outs[n + i][1]), what
 
 
-# One head per KV head: a work item is 256 (or 384) rows of one head, so the
-# item count is Hq * ceil(R / rows).  One descriptor leaves room for 424 words.
+# One head per KV head and both chunks of a degree of 1 within a block (R > 1):
+# two work items per head.  One descriptor leaves room for 424 words, two for
+# 400, 17 for 40.
 @pytest.mark.parametrize("rows", [256, 384])
-@pytest.mark.parametrize("R,H,n_descs", [(1, 1, 1), (60, 424, 1), (60, 425, 1), (400, 106, 2), (40, 8, 17),
-                                         (40, 8, 33)])
+@pytest.mark.parametrize("R,H,n_descs", [(1, 1, 1), (60, 212, 1), (60, 213, 1), (400, 100, 2), (400, 101, 2),
+                                         (1, 2, 17), (1, 3, 17), (1, 1, 33)])
 def test_tables_on_both_sides_of_the_argument_space(rows, R, H, n_descs):
     try:
         cp.set_workgroup_rows(rows)
