@@ -922,12 +922,19 @@ std::mutex g_stage_mu;
 Slot g_slots[kSlots];
 int g_next_slot = 0;
 
-// Waits until the slot's pending upload has read it.
+// Waits until the slot's pending upload has read it.  A wait of seconds may
+// mean that the device is lost: then the runtime is asked.
 int wait_slot(Slot& s) {
   const uint32_t* done = reinterpret_cast<const uint32_t*>(s.host + s.words_at);
+  int spins = 0;
   for (size_t i = 0; i < s.n_words; ++i)
-    for (int spins = 0; __atomic_load_n(done + i, __ATOMIC_ACQUIRE) == 0; ++spins)
-      if (spins > 1000) std::this_thread::sleep_for(std::chrono::microseconds(10));
+    while (__atomic_load_n(done + i, __ATOMIC_ACQUIRE) == 0) {
+      if (++spins < 1000) continue;
+      std::this_thread::sleep_for(std::chrono::microseconds(10));
+      if (spins % 200000 != 0) continue;
+      const hipError_t e = hipDeviceSynchronize();
+      if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("waiting for a table upload: ") + hipGetErrorString(e));
+    }
   s.n_words = 0;
   if (s.ev_pending) {
     const hipError_t e = hipEventSynchronize(s.ev);
