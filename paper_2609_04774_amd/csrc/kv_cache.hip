@@ -22,13 +22,15 @@
 // 20.7; a 128K request of eight re-sharded (two tensors at once) 180 -> 170 us
 // (6.3 TB/s).
 //
-// Stores carry non-temporal hints, and so do loads except the write-back's up
-// to the size of the 256 MB Infinity Cache, which may hold the rows its caller
-// has just computed: a rank's 16384 rows of the 128K prompt take 20.7 us (6.5
-// TB/s) whether a cache holds them or not, with streaming loads 24-27, and with
-// plain stores 28 when none does.  Beyond that size, and for the gather and the
-// re-shard, streaming loads are the faster: 131000 rows written back 200
-// against 206 us, a 48K prefix gathered 69 against 73.
+// Stores carry non-temporal hints, and so do the gather's loads (a cached prefix
+// is seldom in a cache: 69 us for 48K tokens, 73 with plain loads), while the
+// write-back and the re-shard load plainly up to the size of the 256 MB Infinity
+// Cache, which may hold the rows their caller has just computed or moved: a
+// rank's 16384 rows of the 128K prompt take 20.7 us (6.5 TB/s) whether a cache
+// holds them or not, with streaming loads 24-27, and with plain stores 28 when
+// none does; a 32K request re-sharded 39 us when one does and 46 when not, with
+// streaming loads 44 both ways.  Beyond that size streaming loads are the
+// faster: 131000 rows written back 200 against 206 us.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void repartition_kernel(RepartitionParams
 
 // Every row of the suffix from its source rank to its destination rank, in
 // kSets row sets at once.
-template <int kLanes, int kSets>
+template <int kLanes, int kSets, bool kStream>
 __global__ __launch_bounds__(kThreads) void repartition_all_kernel(RepartitionAllParams p) {
   const int64_t i = row_index<kLanes>();
   if (i >= p.R) return;
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void repartition_all_kernel(RepartitionAl
     src[s] = p.src[s][from.rank] + from.row * p.row_bytes;
     dst[s] = p.dst[s][to.rank] + to.row * p.row_bytes;
   }
-  copy_rows<kLanes, kSets>(src, dst, p.row_bytes, threadIdx.x % kLanes);
+  copy_rows<kLanes, kSets, kStream>(src, dst, p.row_bytes, threadIdx.x % kLanes);
 }
 
 // A block-table entry outside the cache gives zero rows.
@@ -174,11 +176,19 @@ int launch_rows(void (*k16)(Params), void (*k32)(Params), void (*k64)(Params), c
 }  // namespace
 
 int launch_repartition_all(const RepartitionAllParams& p, void* stream) {
+  const bool streamed = p.n_sets * p.R * p.row_bytes > kInfinityCacheBytes;
+  auto launch = [&](auto k16, auto k32, auto k64) {
+    return launch_rows<RepartitionAllParams>(k16, k32, k64, p, p.R, "cp_repartition_all", stream);
+  };
   if (p.n_sets == 2)
-    return launch_rows(repartition_all_kernel<16, 2>, repartition_all_kernel<32, 2>, repartition_all_kernel<64, 2>, p,
-                       p.R, "cp_repartition_all", stream);
-  return launch_rows(repartition_all_kernel<16, 1>, repartition_all_kernel<32, 1>, repartition_all_kernel<64, 1>, p,
-                     p.R, "cp_repartition_all", stream);
+    return streamed ? launch(repartition_all_kernel<16, 2, true>, repartition_all_kernel<32, 2, true>,
+                             repartition_all_kernel<64, 2, true>)
+                    : launch(repartition_all_kernel<16, 2, false>, repartition_all_kernel<32, 2, false>,
+                             repartition_all_kernel<64, 2, false>);
+  return streamed ? launch(repartition_all_kernel<16, 1, true>, repartition_all_kernel<32, 1, true>,
+                           repartition_all_kernel<64, 1, true>)
+                  : launch(repartition_all_kernel<16, 1, false>, repartition_all_kernel<32, 1, false>,
+                           repartition_all_kernel<64, 1, false>);
 }
 
 int launch_gather(const GatherParams& p, void* stream) {

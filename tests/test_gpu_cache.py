@@ -298,8 +298,9 @@ def test_every_row_width_moves_whole(Hkv, D):
 
 
 @pytest.mark.parametrize("R", [65536, 65537])
-def test_writeback_on_both_sides_of_the_infinity_cache(R):
-    """256 MB of rows, and just more (streaming loads)."""
+def test_copies_on_both_sides_of_the_infinity_cache(R):
+    """256 MB of rows, and just more (streaming loads): written back and
+    gathered, and re-sharded in two steps, two row sets at once and alone."""
     k, v = (torch.randint(-2 ** 15, 2 ** 15, (R, 8, 128), dtype=torch.int16, device=DEV).view(torch.bfloat16)
             for _ in range(2))
     table = torch.randperm(R // 16 + 1, device=DEV).to(torch.int32)
@@ -309,3 +310,17 @@ def test_writeback_on_both_sides_of_the_infinity_cache(R):
     cp.kv_gather(kc, vc, table, 0, ko, vo)
     for a, b in ((k, ko), (v, vo)):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    half = [[torch.zeros(cp.shard_plan(0, R, 2, r, with_rows=False)[0].n_rows, 8, 128, dtype=torch.bfloat16,
+                         device=DEV) for r in range(2)] for _ in range(2)]
+    cp.repartition_all(0, R, [[k], [v]], half)
+    cp.repartition_all(0, R, half, [[ko.zero_()], [vo.zero_()]])
+    for a, b in ((k, ko), (v, vo)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    n = 2 * R  # one set of as many bytes
+    one = torch.cat([k, v])
+    back = torch.zeros_like(one)
+    parts = [torch.zeros(cp.shard_plan(0, n, 2, r, with_rows=False)[0].n_rows, 8, 128, dtype=torch.bfloat16,
+                         device=DEV) for r in range(2)]
+    cp.repartition_all(0, n, [[one]], [parts])
+    cp.repartition_all(0, n, [parts], [[back]])
+    assert torch.equal(one.view(torch.int16), back.view(torch.int16))
