@@ -897,6 +897,13 @@ PartialParams partial_params(const Plan& plan, const Layout& lay, unsigned char*
   return p;
 }
 
+bool capturing(void* stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing((hipStream_t)stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
 }  // namespace cpattn
 
 namespace {
@@ -905,17 +912,13 @@ namespace {
 // device's address space and coherent (the device reads it over the bus,
 // never from a cached copy): the upload kernel reads it (upload.hip).  A slot
 // is reused only after the upload that read it is done with it: the kernel's
-// blocks write the words after the tables, or, where the upload was captured
-// into a graph, its event says so.
+// blocks write the words after the tables.  Captured uploads take no slot.
 struct Slot {
   unsigned char* host = nullptr;
   void* mapped = nullptr;  // the same memory as the device addresses it
   size_t cap = 0;
-  hipEvent_t ev = nullptr;
-  int device = -1;
   size_t words_at = 0;   // the pending upload's words
   size_t n_words = 0;    // 0: none pending
-  bool ev_pending = false;
 };
 constexpr int kSlots = 8;
 std::mutex g_stage_mu;
@@ -936,35 +939,16 @@ int wait_slot(Slot& s) {
       if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("waiting for a table upload: ") + hipGetErrorString(e));
     }
   s.n_words = 0;
-  if (s.ev_pending) {
-    const hipError_t e = hipEventSynchronize(s.ev);
-    if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventSynchronize: ") + hipGetErrorString(e));
-    s.ev_pending = false;
-  }
-  return CP_OK;
-}
-
-int record_slot(Slot& s, hipStream_t stream) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
-  if (s.ev && s.device != dev) {
-    (void)hipEventDestroy(s.ev);
-    s.ev = nullptr;
-  }
-  if (!s.ev) {
-    e = hipEventCreateWithFlags(&s.ev, hipEventDisableTiming);
-    if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventCreate: ") + hipGetErrorString(e));
-    s.device = dev;
-  }
-  e = hipEventRecord(s.ev, stream);
-  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
-  s.ev_pending = true;
   return CP_OK;
 }
 
 int stage_and_copy(const Plan& plan, const Layout& lay, void* dst, hipStream_t stream) {
   const size_t bytes = lay.pieces;  // the tables; a multiple of 256
+  if (capturing(stream)) {
+    std::vector<unsigned char> host(bytes);
+    pack_tables(plan, lay, host.data());
+    return cpattn::launch_upload(dst, host.data(), bytes, stream);
+  }
   const size_t n_words = upload_blocks(bytes);
   std::lock_guard<std::mutex> lock(g_stage_mu);
   Slot& s = g_slots[g_next_slot];
@@ -987,14 +971,8 @@ int stage_and_copy(const Plan& plan, const Layout& lay, void* dst, hipStream_t s
   }
   pack_tables(plan, lay, s.host);
   std::memset(s.host + bytes, 0, 4 * n_words);
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
-    (void)hipGetLastError();
-    capture = hipStreamCaptureStatusNone;
-  }
   st = cpattn::launch_upload(dst, s.mapped, bytes, stream);
   if (st != CP_OK) return st;
-  if (capture != hipStreamCaptureStatusNone) return record_slot(s, stream);
   s.words_at = bytes;
   s.n_words = n_words;
   return CP_OK;

@@ -190,11 +190,15 @@ int launch_partial(const PartialParams& p, void* stream);
 // device's address space to device memory, with a kernel on `stream`
 // (upload.hip).  The source is followed by upload_blocks(bytes) 32-bit words:
 // block b of the kernel writes 1 to word b when it has read its part of the
-// source (not when the stream is being captured: a graph may run the kernel
-// again after the memory has another use).
+// source.  A graph runs its kernels again after that memory has another use:
+// on a stream that is being captured the source is any host memory, read before
+// the call returns, and the bytes travel as kernel arguments (no words).
 constexpr size_t kUploadBlockBytes = 4096;
 inline size_t upload_blocks(size_t bytes) { return (bytes + kUploadBlockBytes - 1) / kUploadBlockBytes; }
 int launch_upload(void* dst, const void* src, size_t bytes, void* stream);
+
+// Whether work on `stream` is being recorded into a graph (cp_attn.cpp).
+bool capturing(void* stream);
 
 // Host planning of one cp_attn_partial launch (cp_attn.cpp), shared by the
 // entry points that take a caller workspace and the one that uses the

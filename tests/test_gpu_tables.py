@@ -92,6 +92,34 @@ def test_a_captured_launch_replays(H):
     torch.cuda.synchronize()
 
 
+def test_a_captured_launch_replays_after_staged_ones():
+    """A graph whose launch has tables beyond the argument space, replayed
+    after more staged launches than there are slots, larger ones among them."""
+    H = 500
+    launch = _launch(200, H, H, 23)
+    ws = gc.new_workspace(launch[0], H, H)
+    others = []
+    for i in range(10):
+        h = 430 + 60 * i
+        others.append((h, _launch(50 + i, h, h, 200 + i)))
+        others[-1] += (gc.new_workspace(others[-1][1][0], h, h),)
+    cp.attn_partial_noalloc(launch[1], H, H)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cp.attn_partial(launch[0], H, H, ws)
+    for _ in range(3):
+        for h, other, w in others:
+            cp.attn_partial(other[0], h, h, w)
+        torch.cuda.synchronize()
+        ws.zero_()
+        launch[2][0][0].zero_()
+        launch[2][0][1].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        _compare(launch, "replay")
+
+
 # (L, P, C, Hq, Hkv, rank): pieces of three or four tiles; six and more per
 # item; 64 per item (a wave merges each row); pieces that some rows see no key
 # of; one and three query rows; a 384-row list of a few pieces per item; head
