@@ -232,7 +232,8 @@ size_t cp_attn_partial_workspace_size(const cp_partial_desc* descs, int32_t n_de
  * the library (allocated on first use, kept until process exit), a ring of
  * eight slots, and a small kernel on `stream` copies them into the workspace:
  * a call that finds its slot not yet read by its last copy blocks the calling
- * host thread until that copy has run (never on the whole device).  A call
+ * host thread until that copy has run (never on the whole device; CP_ERR_HIP
+ * when the runtime reports after seconds that it will not run).  A call
  * whose stream is being captured into a graph stages nothing: its tables are
  * kernel arguments whatever their size, in several launches where needed, and
  * the graph keeps them.

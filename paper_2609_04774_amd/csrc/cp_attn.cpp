@@ -914,30 +914,74 @@ namespace {
 // is reused only after the upload that read it is done with it: the kernel's
 // blocks write the words after the tables.  Captured uploads take no slot.
 struct Slot {
+  std::mutex mu;           // held while the slot is waited for, filled and launched from
   unsigned char* host = nullptr;
   void* mapped = nullptr;  // the same memory as the device addresses it
   size_t cap = 0;
-  size_t words_at = 0;   // the pending upload's words
-  size_t n_words = 0;    // 0: none pending
+  size_t words_at = 0;     // the pending upload's words
+  size_t n_words = 0;      // 0: none pending
+  int device = 0;          // where the pending upload runs
+  hipStream_t stream = nullptr;
 };
 constexpr int kSlots = 8;
-std::mutex g_stage_mu;
 Slot g_slots[kSlots];
-int g_next_slot = 0;
+std::atomic<unsigned> g_next_slot{0};
 
-// Waits until the slot's pending upload has read it.  A wait of seconds may
-// mean that the device is lost: then the runtime is asked.
+// What the runtime says of the slot's stream, without waiting for it:
+// hipErrorNotReady while it has work to do.  Not asked: a stream that is being
+// captured now, and another thread's hipStreamPerThread.  A thread may ask while
+// others capture in global mode only in relaxed mode.
+hipError_t query_slot(const Slot& s) {
+  if (s.stream == hipStreamPerThread) return hipErrorNotReady;
+  int current = 0;
+  hipError_t e = hipGetDevice(&current);
+  if (e != hipSuccess) return e;
+  if (current != s.device && (e = hipSetDevice(s.device)) != hipSuccess) return e;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e == hipSuccess) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(s.stream, &status);
+    if (e == hipErrorStreamCaptureImplicit || (e == hipSuccess && status != hipStreamCaptureStatusNone))
+      e = hipErrorNotReady;
+    else
+      e = hipStreamQuery(s.stream);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  (void)hipGetLastError();  // "not ready" is no error of a later call's
+  if (current != s.device) (void)hipSetDevice(current);
+  return e;
+}
+
+// Waits until the slot's pending upload has read it.  The stream may have any
+// amount of work before the upload, but one that has failed or is gone never
+// gets there: a wait of seconds asks the runtime.
 int wait_slot(Slot& s) {
   const uint32_t* done = reinterpret_cast<const uint32_t*>(s.host + s.words_at);
-  int spins = 0;
-  for (size_t i = 0; i < s.n_words; ++i)
-    while (__atomic_load_n(done + i, __ATOMIC_ACQUIRE) == 0) {
-      if (++spins < 1000) continue;
-      std::this_thread::sleep_for(std::chrono::microseconds(10));
-      if (spins % 200000 != 0) continue;
-      const hipError_t e = hipDeviceSynchronize();
-      if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("waiting for a table upload: ") + hipGetErrorString(e));
+  size_t n_read = 0;
+  auto read = [&] {
+    while (n_read < s.n_words && __atomic_load_n(done + n_read, __ATOMIC_ACQUIRE) != 0) ++n_read;
+    return n_read == s.n_words;
+  };
+  constexpr std::chrono::seconds kAskEvery(2);
+  std::chrono::steady_clock::time_point ask = std::chrono::steady_clock::time_point::max();
+  for (int spins = 0; !read(); spins += spins < 1000) {
+    if (spins < 1000) continue;
+    const std::chrono::steady_clock::time_point now = std::chrono::steady_clock::now();
+    if (ask == std::chrono::steady_clock::time_point::max()) ask = now + kAskEvery;
+    if (now >= ask) {
+      const hipError_t e = query_slot(s);
+      if (e != hipErrorNotReady && !read()) {
+        // Whether anything still reads the memory is unknown: it is left.
+        s.host = nullptr;
+        s.mapped = nullptr;
+        s.cap = s.n_words = 0;
+        return fail(CP_ERR_HIP, std::string("cp_attn_partial: an earlier table upload did not run: ") + hipGetErrorString(e));
+      }
+      ask = now + kAskEvery;
     }
+    std::this_thread::sleep_for(std::chrono::microseconds(10));
+  }
   s.n_words = 0;
   return CP_OK;
 }
@@ -950,11 +994,13 @@ int stage_and_copy(const Plan& plan, const Layout& lay, void* dst, hipStream_t s
     return cpattn::launch_upload(dst, host.data(), bytes, stream);
   }
   const size_t n_words = upload_blocks(bytes);
-  std::lock_guard<std::mutex> lock(g_stage_mu);
-  Slot& s = g_slots[g_next_slot];
-  g_next_slot = (g_next_slot + 1) % kSlots;
+  Slot& s = g_slots[g_next_slot.fetch_add(1) % kSlots];
+  std::lock_guard<std::mutex> lock(s.mu);
   int st = wait_slot(s);
   if (st != CP_OK) return st;
+  hipError_t e = hipGetDevice(&s.device);
+  if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
+  s.stream = stream;
   if (s.cap < bytes + 4 * n_words) {
     if (s.host) (void)hipHostFree(s.host);
     s.host = nullptr;
@@ -962,7 +1008,7 @@ int stage_and_copy(const Plan& plan, const Layout& lay, void* dst, hipStream_t s
     s.cap = 0;
     const size_t cap = std::max<size_t>(bytes + 4 * n_words, 64 * 1024);
     void* host = nullptr;
-    hipError_t e = hipHostMalloc(&host, cap, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
+    e = hipHostMalloc(&host, cap, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
     if (e != hipSuccess) return fail(CP_ERR_HIP, std::string("hipHostMalloc (staging): ") + hipGetErrorString(e));
     s.host = static_cast<unsigned char*>(host);
     e = hipHostGetDevicePointer(&s.mapped, s.host, 0);
