@@ -30,7 +30,8 @@
  *   - The head dimension D is 128; paged KV blocks hold 16 tokens.
  *   - Partial outputs are normalised: O = sum_j e^{x_j - LSE} v_j over the
  *     partial's keys, LSE = ln sum_j e^{x_j} (natural log, x_j = scale*q.k).
- *     A row that sees no key has O = 0 and LSE = -inf.
+ *     A row that sees no key has O = 0 and LSE = -inf; a row with a NaN among
+ *     its scores has O = NaN and LSE = -inf.
  *   - The caller owns every buffer and the stream.  No call allocates device
  *     memory, synchronises the device, or keeps pointers after returning
  *     (cp_attn_partial_noalloc waits for its stream before reusing its

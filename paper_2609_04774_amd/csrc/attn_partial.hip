@@ -974,12 +974,15 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_partial_kernel(const DevD
     const float ltb = psum[b][0];
     const bool live = (m_run[b] > 0.5f * kNoMax) && (lt > 0.f) && (ltb > 0.f);
     const float inv = live ? 1.f / ltb : 0.f;
-    const float lse = live ? m_run[b] * kLn2 + logf(lt) : -INFINITY;
+    // A NaN among the row's scores makes its sums NaN: O = NaN * 0, LSE = -inf.
+    float lse = live ? m_run[b] * kLn2 + logf(lt) : -INFINITY;
     float* orow;
     float* lrow;
     if (it.piece >= 0) {
       // One piece of a split walk: its partial over its keys goes to the
-      // piece slot (row 16 * block + query of the work item).
+      // piece slot (row 16 * block + query of the work item).  There a NaN sum
+      // is an LSE of NaN, which the merge tells from a piece without keys.
+      if (lt != lt) lse = lt;
       unsigned char* slot = p.pieces + (size_t)it.piece * piece_bytes(kWaves * kBlockRows * NB);
       const int r = (NB * wave + b) * kBlockRows + l16;
       orow = reinterpret_cast<float*>(slot) + (size_t)r * kHeadDim;
@@ -1005,7 +1008,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_partial_kernel(const DevD
 
 // Exact combination of a split work item's pieces (disjoint key sets of the
 // same rows): LSE = M + ln sum_k e^{LSE_k - M}, O = sum_k e^{LSE_k - LSE} O_k,
-// a piece with LSE_k = -inf weighing 0 (and not read).  Each row of the item
+// a piece with LSE_k = -inf weighing 0 (and not read).  A piece with LSE_k = NaN
+// makes the row what the unsplit item would: O = NaN, LSE = -inf.  Each row
 // is written to the descriptor's output where the unsplit item would have
 // written it.
 //
@@ -1060,10 +1064,10 @@ __global__ __launch_bounds__(kMergeThreads) void split_merge_kernel(const DevDes
   for (int j = 0; j < kPer; ++j) {
     const int k = lane + j * kLanes;
     l[j] = k < sp.n_pieces ? reinterpret_cast<const float*>(slots + (size_t)k * slot_bytes + o_bytes)[r] : -INFINITY;
-    m = fmaxf(m, l[j]);
+    m = __builtin_elementwise_maximum(m, l[j]);  // NaN if either is
   }
 #pragma unroll
-  for (int k = 1; k < kLanes; k *= 2) m = fmaxf(m, __shfl_xor(m, k));
+  for (int k = 1; k < kLanes; k *= 2) m = __builtin_elementwise_maximum(m, __shfl_xor(m, k));
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   float lse = -INFINITY;
   if (m != -INFINITY) {
@@ -1113,7 +1117,7 @@ __global__ __launch_bounds__(kMergeThreads) void split_merge_kernel(const DevDes
     acc.y *= inv;
     acc.z *= inv;
     acc.w *= inv;
-    lse = m + logf(total);
+    if (m == m) lse = m + logf(total);
   }
   if (half == 0) reinterpret_cast<float4*>(d.o + (row * p.Hq + head) * kHeadDim)[col] = acc;
   if (lane == 0) d.lse[row * p.Hq + head] = lse;

@@ -181,3 +181,34 @@ def test_merge_of_every_partial_count(n):
         assert float((Lo.cpu().double() - L)[live].abs().max()) < 5e-6
         assert float((O.cpu().double() - ref).abs().max()) < 1e-5
         assert bool(((Ob.cpu().double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all())
+
+
+# (L, P, C, Hq, Hkv, cut): a launch whose walks are cut (few key tiles a piece;
+# a cached prefix; a wave per merged row) or, with many heads, not.
+@pytest.mark.parametrize("L,P,Hq,Hkv,cut", [(1024, 0, 32, 8, True), (1348, 1248, 32, 8, True),
+                                            (4099, 4096, 16, 1, True), (600, 0, 512, 128, False)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_poisoned_score_shows_cut_or_not(L, P, Hq, Hkv, cut, bad):
+    """A key or a query row that makes scores NaN (+inf does by inf - inf)
+    leaves O = NaN and LSE = -inf in every row that meets it, whether or not
+    the row's walk is cut.  Rows that do not meet it keep their values, but for
+    the running max that P is rounded against (bf16, half an ulp each way)."""
+    prob = Problem(L, P, 1, Hq, Hkv, 41)
+    clean, clean_lse, plan, _ = prob.gpu_rank(0)
+    dv = prob.dev()
+    desc = cp.make_desc(plan, dv["q"], dv["k"], dv["v"], clean, clean_lse, dv.get("kc"), dv.get("vc"), dv.get("bt"))
+    assert (cp.workspace_size([desc], Hq, Hkv) > 1 << 20) == cut
+    R, G, pos = L - P, Hq // Hkv, 2 * (L - P) // 3
+    dv["k"][pos, 0, 5] = bad  # KV head 0's key at suffix index pos
+    dv["q"][R // 2, Hq - 1] = float("nan")
+    o, lse, _, _ = prob.gpu_rank(0)
+    met = torch.zeros(R, Hq, dtype=torch.bool, device=DEV)
+    met[pos:, :G] = True
+    met[R // 2, Hq - 1] = True
+    hit = met.clone()
+    if bad == float("inf"):  # a score of -inf is a key of weight 0
+        hit[pos:, :G] &= ~(dv["q"][pos:, :G, 5] < 0)
+    assert bool(o[hit].isnan().all()) and bool(torch.isneginf(lse[hit]).all())
+    assert bool(torch.isfinite(o[~hit]).all()) and bool(torch.isfinite(lse[~hit]).all())
+    assert float((o - clean)[~met].abs().max()) <= 2.0 ** -8 * float(dv["v"].float().abs().max())
+    assert float((lse - clean_lse)[~met].abs().max()) <= 1e-5
