@@ -225,9 +225,10 @@ size_t cp_attn_partial_workspace_size(const cp_partial_desc* descs, int32_t n_de
  *               stream is past this work.
  * The work list is planned on the host; the lists of the last 16 launches
  * are kept (keyed by every non-pointer field of the descriptors, the head
- * counts and the pinned workgroup shape, matched exactly), so a launch of
- * the same geometry with other buffers, such as the next layer's, reuses its
- * list instead of planning it again.
+ * counts and the pinned workgroup shape, matched exactly, and by the workspace
+ * where the list depends on it), so a launch of the same geometry with other
+ * buffers, such as the next layer's, reuses its list instead of planning it
+ * again.
  * The descriptors and the work list of a small launch (up to 3.5 KB) are
  * kernel arguments.  Larger tables are staged in pinned host memory owned by
  * the library (allocated on first use, kept until process exit), a ring of

@@ -206,7 +206,7 @@ constexpr double kBalanceSlack = 1.03;
 // long cached prefix), where fill's remainders are too long for the room
 // they find.  Returns each item's interior cut points (tile indices,
 // ascending) in `cuts` (indexed by the items' numbers, allocated only when a
-// cut is made).
+// cut is made), of at most max_pieces pieces.
 struct ItemTiles {
   int64_t item;   // the item's number in the launch
   int64_t tiles;  // its key walk
@@ -228,8 +228,8 @@ int64_t list_schedule(const std::vector<int64_t>& loads, const std::vector<int64
 
 typedef std::vector<std::vector<int32_t>> Cuts;  // per item (position in the list): cut points
 
-// The fill candidate (see balance_cuts).
-Cuts fill_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t ideal, int64_t limit) {
+// The fill candidate (see balance_cuts), of at most max_pieces pieces.
+Cuts fill_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t ideal, int64_t limit, int64_t max_pieces) {
   struct Seg {
     int64_t len;
     size_t idx;
@@ -241,13 +241,16 @@ Cuts fill_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t ideal, 
   auto longer = [](const Seg& a, const Seg& b) { return a.len < b.len || (a.len == b.len && a.idx > b.idx); };
   std::priority_queue<Seg, std::vector<Seg>, decltype(longer)> queue(longer);
   for (size_t i = 0; i < items.size(); ++i) queue.push(Seg{items[i].tiles, i, 0});
+  int64_t pieces = 0;
   while (!queue.empty()) {
     const Seg s = queue.top();
     queue.pop();
     const int64_t load = units.top();
     units.pop();
     int64_t take = s.len;
-    if (load + s.len + kItemSetupTiles > limit && (int64_t)c[s.idx].size() + 1 < kMaxPieces) {
+    const int64_t more = c[s.idx].empty() ? 2 : 1;  // pieces that a cut here adds
+    if (load + s.len + kItemSetupTiles > limit && (int64_t)c[s.idx].size() + 1 < kMaxPieces &&
+        pieces + more <= max_pieces) {
       // Fill this unit up to the ideal, or give it the smallest piece when
       // it is there already.
       const int64_t room = ideal - load - kItemSetupTiles;
@@ -255,6 +258,7 @@ Cuts fill_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t ideal, 
     }
     units.push(load + take + kItemSetupTiles);
     if (take < s.len) {
+      pieces += more;
       c[s.idx].push_back(s.t0 + (int32_t)take);
       queue.push(Seg{s.len - take, s.idx, s.t0 + (int32_t)take});
     }
@@ -333,7 +337,7 @@ std::pair<int64_t, int64_t> score_cuts(const std::vector<ItemTiles>& items, cons
   return std::make_pair(list_schedule(std::vector<int64_t>(n_units, 0), lens), pieces);
 }
 
-void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_items_total, Cuts* cuts) {
+void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_items_total, int64_t max_pieces, Cuts* cuts) {
   if (items.empty()) return;
   int64_t total = 0, longest = 0;
   for (const ItemTiles& it : items) {
@@ -351,12 +355,13 @@ void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_ite
   Cuts chosen;
   auto consider = [&](Cuts c) {
     const std::pair<int64_t, int64_t> sc = score_cuts(items, c, n_units);
+    if (sc.second > max_pieces) return;
     if (sc.first < best.first || (sc.first == best.first && sc.second < best.second)) {
       best = sc;
       chosen.swap(c);
     }
   };
-  consider(fill_cuts(items, n_units, ideal, limit));
+  consider(fill_cuts(items, n_units, ideal, limit, max_pieces));
   for (int m = 1; m <= 4; ++m) consider(even_cuts(items, n_units, limit, m));
   if (chosen.empty()) return;
   for (size_t i = 0; i < items.size(); ++i) {
@@ -435,8 +440,10 @@ int schedules_of(int n_groups) { return n_groups % kXcds == 0 ? kXcds : 1; }
 // The work list of one launch for one workgroup shape: items, split items and
 // piece count into *out (whose descriptors are set).  cap > 0: every walk cut
 // to at most that many tiles; cap = 0: balance cuts where they pay (few items
-// with a pinned shape: equal pieces, see kPinnedBelowItems).
-int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap, Plan* out) {
+// with a pinned shape: equal pieces, see kPinnedBelowItems), of at most
+// max_pieces pieces.
+int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap, Plan* out,
+               int64_t max_pieces = INT64_MAX) {
   struct Cand {
     int64_t cost;
     WorkItem w;
@@ -468,7 +475,7 @@ int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap
       for (size_t bi = 0; bi < blocks.size(); ++bi)
         if (blocks[bi].tiles > 0)
           for (int g = x; g < n_groups; g += n_sched) sched.push_back(ItemTiles{(int64_t)(bi * n_groups + g), blocks[bi].tiles});
-      balance_cuts(sched, kComputeUnits / n_sched, blocks.size() * n_groups, &cuts);
+      balance_cuts(sched, kComputeUnits / n_sched, blocks.size() * n_groups, max_pieces / n_sched, &cuts);
     }
   }
   out->splits.clear();
@@ -584,13 +591,25 @@ double estimate_us(const Plan& plan) {
   return slowed(end, sum, kComputeUnits) + merge_us(plan.shape, plan.n_pieces, (int64_t)plan.splits.size());
 }
 
-// A candidate list of one shape: its walks cut to `cap` tiles (0: plan_items'
-// balance cuts), its estimate and the bytes of its piece slots.
+size_t align_up(size_t x) { return (x + kItemsAlign - 1) / kItemsAlign * kItemsAlign; }
+
+// The workspace of a list of so many entries.
+Layout layout_of_counts(size_t n_descs, size_t n_items, size_t n_splits, size_t n_pieces, int rows) {
+  Layout l;
+  l.items = align_up(n_descs * sizeof(DevDesc));
+  l.splits = align_up(l.items + n_items * sizeof(WorkItem));
+  l.pieces = align_up(l.splits + n_splits * sizeof(SplitItem));
+  l.total = l.pieces + n_pieces * piece_bytes(rows);
+  return l;
+}
+
+// A candidate list of one shape: its walks cut to `cap` tiles, its estimate,
+// the bytes of its piece slots and of its workspace.
 struct Choice {
-  int rows = 0;
-  int64_t cap = 0;
-  double us = 0.0;
-  size_t slots = 0;
+  const Blocks* blocks;
+  int64_t cap;
+  double us;
+  size_t slots, total;
 };
 
 // The same estimate for a list cut to `cap` tiles, without building it.
@@ -615,18 +634,21 @@ Choice estimate_cap(const Blocks& b, int64_t cap, std::vector<std::pair<int64_t,
   for (const std::pair<int64_t, int64_t>& len : *lens)
     for (int64_t i = 0; i < len.second; ++i) units.add(len.first * tile_us(b.shape) + kItemSetupUs);
   Choice c;
-  c.rows = b.shape.rows_per_wg;
+  c.blocks = &b;
   c.cap = cap;
   c.us = slowed(units.end, units.sum, n_units) + merge_us(b.shape, n_pieces, n_splits);
   c.slots = (size_t)n_pieces * piece_bytes(b.shape.rows_per_wg);
+  c.total = 0;
   return c;
 }
 
 // Adds one shape's candidates: the longest walk cut into k = 1, 2, ... equal
 // pieces and every other walk to that length.  Once the even spread of a cut
 // list over the units, and its merge, alone end after the best candidate
-// (*best), more pieces only add to both: there the search stops.
-void add_choices(const Blocks& b, int64_t target_pieces, double* best, std::vector<Choice>* out) {
+// (*best), or its workspace exceeds `limit`, more pieces only add to them: there
+// the search stops.
+void add_choices(const Blocks& b, size_t n_descs, int64_t target_pieces, size_t limit, double* best,
+                 std::vector<Choice>* out) {
   std::vector<std::pair<int64_t, int64_t>> lens;
   int64_t last = 0;
   for (int64_t k = 1; k <= kMaxPieces; ++k) {
@@ -634,21 +656,25 @@ void add_choices(const Blocks& b, int64_t target_pieces, double* best, std::vect
     if (k > 1 && (cap < kMinPieceTiles || target_pieces == 0)) break;
     if (cap == last) continue;
     last = cap;
-    int64_t n = 0, n_pieces = 0, shortest = b.max_tiles;
+    int64_t n = 0, n_pieces = 0, n_splits = 0, shortest = b.max_tiles;
     for (const Block& x : b.list) {
       const int64_t m = pieces_at(x.tiles, cap);
       n += m;
       if (m > 1) {
         n_pieces += m;
+        ++n_splits;
         shortest = std::min(shortest, x.tiles / m);
       }
     }
     n *= b.n_groups;
     n_pieces *= b.n_groups;
+    const size_t total = layout_of_counts(n_descs, n, n_splits * b.n_groups, n_pieces, b.shape.rows_per_wg).total;
+    if (total > limit) break;
     if (k > 1 && (n_pieces > target_pieces || shortest < kMinPieceTiles)) break;
     const double spread = (b.all_tiles * tile_us(b.shape) + n * kItemSetupUs) / kComputeUnits;
     if (k > 1 && slowed(spread, spread, 1) + merge_us(b.shape, n_pieces, 1) >= *best) break;
     out->push_back(estimate_cap(b, cap, &lens));
+    out->back().total = total;
     *best = std::min(*best, out->back().us);
   }
 }
@@ -690,13 +716,17 @@ namespace cpattn {
 // chunks and key ranges and on the heads, never on their buffers), so the
 // list of a launch whose key matches is reused instead of planned again:
 // the key holds every non-pointer field of the converted descriptors, the
-// head counts, the piece target and the pinned shape, and matches exactly.
+// head counts, the piece target and the pinned shape, and matches exactly.  A
+// list planned for a workspace of `limit` bytes serves any that holds it and is
+// no larger (what fits there was among its candidates); `wanted` is the size
+// of the unlimited plan.
 struct CachedPlan {
   std::vector<int64_t> key;
   std::vector<WorkItem> items;
   std::vector<SplitItem> splits;
   int64_t n_pieces;
   Shape shape;
+  size_t total, limit, wanted;
 };
 constexpr size_t kPlanCacheSize = 16;
 static std::mutex g_plan_cache_mu;
@@ -715,10 +745,13 @@ static std::vector<int64_t> plan_key(const std::vector<DevDesc>& descs, int32_t 
   return k;
 }
 
-static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out);
+static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out,
+                         size_t limit = SIZE_MAX, size_t* wanted = nullptr);
 
-static int build_plan_rows(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv,
-                           int64_t target_pieces, int forced, bool join, Plan* out) {
+// The plan of a launch in `limit` bytes of workspace; *wanted is the size of
+// the unlimited one.
+static int build_plan_limited(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv,
+                              int64_t target_pieces, size_t limit, Plan* out, size_t* wanted) {
   int st = check_heads(Hq, Hkv, "cp_attn_partial");
   if (st != CP_OK) return st;
   if (n_descs < 0) return fail(CP_ERR_INVALID, "cp_attn_partial: n_descs < 0");
@@ -728,74 +761,81 @@ static int build_plan_rows(const cp_partial_desc* descs, int32_t n_descs, int32_
     st = to_dev(descs[i], i, &out->descs[i]);
     if (st != CP_OK) return st;
   }
-  if (join)
+  const int forced = g_forced_rows.load();
+  if (forced == 0)
     for (DevDesc& d : out->descs) join_chunks(&d);
   std::vector<int64_t> key = plan_key(out->descs, Hq, Hkv, target_pieces, forced);
   {
     std::lock_guard<std::mutex> lock(g_plan_cache_mu);
     for (size_t i = g_plan_cache.size(); i-- > 0;) {
       const CachedPlan& c = g_plan_cache[i];
-      if (c.key != key) continue;
+      if (c.total > limit || limit > c.limit || c.key != key) continue;
       out->items = c.items;
       out->splits = c.splits;
       out->n_pieces = c.n_pieces;
       out->shape = c.shape;
+      *wanted = c.wanted;
       ++g_plan_cache_hits;
       return CP_OK;
     }
   }
-  st = plan_uncached(Hq, Hkv, target_pieces, forced, out);
+  st = plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, wanted);
   if (st != CP_OK) return st;
+  const size_t total = layout_of(*out).total;
+  if (total > limit) return CP_OK;  // the caller refuses it
+  if (*wanted <= limit) limit = SIZE_MAX;
   std::lock_guard<std::mutex> lock(g_plan_cache_mu);
   if (g_plan_cache.size() == kPlanCacheSize) g_plan_cache.erase(g_plan_cache.begin());
-  g_plan_cache.push_back(CachedPlan{std::move(key), out->items, out->splits, out->n_pieces, out->shape});
+  g_plan_cache.push_back(
+      CachedPlan{std::move(key), out->items, out->splits, out->n_pieces, out->shape, total, limit, *wanted});
   return CP_OK;
 }
 
 int build_plan(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, int64_t target_pieces,
                Plan* out) {
-  const int forced = g_forced_rows.load();
-  return build_plan_rows(descs, n_descs, Hq, Hkv, target_pieces, forced, forced == 0, out);
+  size_t wanted = 0;
+  return build_plan_limited(descs, n_descs, Hq, Hkv, target_pieces, SIZE_MAX, out, &wanted);
 }
 
 int build_plan_within(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, size_t bytes, Plan* out,
                       Layout* lay, size_t* wanted) {
-  const int forced = g_forced_rows.load();
-  *wanted = 0;
-  // Fewer pieces, down to none, then the shape with the shortest work list.
-  for (int64_t target = kTargetPieces;; target = target >= 4 ? target / 2 : 0) {
-    const int st = build_plan_rows(descs, n_descs, Hq, Hkv, target, forced, forced == 0, out);
-    if (st != CP_OK) return st;
-    *lay = layout_of(*out);
-    if (*wanted == 0) *wanted = lay->total;
-    if (lay->total <= bytes) return CP_OK;
-    if (out->n_pieces == 0 || target == 0) break;
-  }
-  if (forced) return CP_OK;
-  const int st = build_plan_rows(descs, n_descs, Hq, Hkv, 0, kRowsLarge, true, out);
+  const int st = build_plan_limited(descs, n_descs, Hq, Hkv, kTargetPieces, bytes, out, wanted);
   if (st == CP_OK) *lay = layout_of(*out);
   return st;
 }
 
-// The work list of a launch whose descriptors are converted (out->descs).
-// The larger shape shares every K/V fragment between more rows (faster per
-// tile) but makes fewer, longer work items, which fill the compute units
-// worse; cuts fill them better but cost set-ups and a merge.
-static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out) {
-  if (forced) return plan_items(list_blocks(out->descs, Hq, Hkv, forced), target_pieces, true, 0, out);
-  const Blocks small = list_blocks(out->descs, Hq, Hkv, kRowsSmall);
-  const Blocks large = list_blocks(out->descs, Hq, Hkv, kRowsLarge);
-  // Launches of many rounds: when the bounds already decide (one shape's worst
-  // case ends before the other's best), only the winner is planned.  Its
-  // worst case is within one item of its even spread, which leaves little to
-  // cuts other than the balance cuts.
-  const Bounds bs = shape_bounds(small), bl = shape_bounds(large);
-  if (bl.hi < bs.lo) return plan_items(large, target_pieces, false, 0, out);
-  if (bs.hi < bl.lo) return plan_items(small, target_pieces, false, 0, out);
+// The list of an unpinned launch whose estimate ends first among those of at most
+// max_pieces pieces and a workspace of at most `limit`; *fits says whether there
+// is any (out is then set).  `whole` is the shape that the bounds decide for, or
+// null.
+static int choose_list(const Blocks& small, const Blocks& large, const Blocks* whole, int64_t target_pieces,
+                       size_t limit, int64_t max_pieces, Plan* out, bool* fits) {
+  const size_t n_descs = out->descs.size();
+  // Balance cuts of as many pieces as the limit leaves room for beside the
+  // uncut list's tables.
+  auto balance = [&](const Blocks& b, Plan* p) {
+    int64_t room = max_pieces;
+    if (limit != SIZE_MAX) {
+      const size_t tables = layout_of_counts(n_descs, b.list.size() * b.n_groups, 0, 0, b.shape.rows_per_wg).total;
+      const size_t piece = piece_bytes(b.shape.rows_per_wg) + sizeof(WorkItem) + sizeof(SplitItem);
+      room = limit > tables + 2 * kItemsAlign
+                 ? std::min(room, (int64_t)((limit - tables - 2 * kItemsAlign) / piece))
+                 : 0;
+    }
+    const int st = plan_items(b, target_pieces, false, 0, p, room);
+    *fits = st == CP_OK && layout_of(*p).total <= limit;
+    return st;
+  };
+  if (whole) {
+    const int st = balance(*whole, out);
+    if (st != CP_OK || *fits) return st;
+  }
   std::vector<Choice> choices;
   double best_us = INFINITY;
-  add_choices(small, target_pieces, &best_us, &choices);
-  add_choices(large, target_pieces, &best_us, &choices);
+  add_choices(small, n_descs, std::min(target_pieces, max_pieces), limit, &best_us, &choices);
+  add_choices(large, n_descs, std::min(target_pieces, max_pieces), limit, &best_us, &choices);
+  *fits = !choices.empty();
+  if (!*fits) return CP_OK;
   const Choice* best = &choices[0];
   for (const Choice& c : choices)
     if (c.us < best->us) best = &c;
@@ -812,7 +852,7 @@ static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int for
     if (within && within->us <= kSlotGain * best->us) best = within;
   }
   const Choice chosen = *best;
-  const int st = plan_items(chosen.rows == kRowsLarge ? large : small, target_pieces, false, chosen.cap, out);
+  const int st = plan_items(*chosen.blocks, target_pieces, false, chosen.cap, out);
   if (st != CP_OK || target_pieces == 0) return st;
   // Long walks: the balance cuts of each shape, where they end sooner.
   double us = chosen.us;
@@ -820,27 +860,64 @@ static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int for
     if (b->max_tiles < 2 * kMinBalancePiece) continue;
     Plan balanced;
     balanced.descs = out->descs;
-    const int st2 = plan_items(*b, target_pieces, false, 0, &balanced);
+    const int st2 = balance(*b, &balanced);
     if (st2 != CP_OK) return st2;
-    if (target_pieces < kTargetPieces && balanced.n_pieces > target_pieces) continue;  // a workspace's limit
+    if (!*fits) continue;
     const double t = estimate_us(balanced);
     if (t < us) {
       us = t;
       *out = std::move(balanced);
     }
   }
+  *fits = true;
   return CP_OK;
 }
 
-static size_t align_up(size_t x) { return (x + kItemsAlign - 1) / kItemsAlign * kItemsAlign; }
+// The work list of a launch whose descriptors are converted (out->descs), in
+// `limit` bytes of workspace: the list of the free choice, or, when that does
+// not fit, of the fastest estimate that does with no more pieces; the shortest
+// list when none fits.
+// *wanted: the workspace of the free choice.
+// The larger shape shares every K/V fragment between more rows (faster per
+// tile) but makes fewer, longer work items, which fill the compute units
+// worse; cuts fill them better but cost set-ups and a merge.
+static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out, size_t limit,
+                         size_t* wanted) {
+  size_t free_size = 0;
+  size_t* const size = wanted ? wanted : &free_size;
+  if (forced) {
+    // A pinned shape: its fixed rule for fewer pieces, down to none.
+    const Blocks b = list_blocks(out->descs, Hq, Hkv, forced);
+    *size = 0;
+    for (int64_t target = target_pieces;; target = target >= 4 ? target / 2 : 0) {
+      const int st = plan_items(b, target, true, 0, out);
+      if (st != CP_OK) return st;
+      const size_t total = layout_of(*out).total;
+      if (*size == 0) *size = total;
+      if (total <= limit || out->n_pieces == 0 || target == 0) return CP_OK;
+    }
+  }
+  const Blocks small = list_blocks(out->descs, Hq, Hkv, kRowsSmall);
+  const Blocks large = list_blocks(out->descs, Hq, Hkv, kRowsLarge);
+  // Launches of many rounds: when the bounds already decide (one shape's worst
+  // case ends before the other's best), only the winner is planned.  Its
+  // worst case is within one item of its even spread, which leaves little to
+  // cuts other than the balance cuts.
+  const Bounds bs = shape_bounds(small), bl = shape_bounds(large);
+  const Blocks* whole = bl.hi < bs.lo ? &large : bs.hi < bl.lo ? &small : nullptr;
+  bool fits = false;
+  int st = choose_list(small, large, whole, target_pieces, SIZE_MAX, INT64_MAX, out, &fits);
+  if (st != CP_OK) return st;
+  *size = layout_of(*out).total;
+  if (*size <= limit) return CP_OK;
+  st = choose_list(small, large, nullptr, target_pieces, limit, out->n_pieces, out, &fits);
+  if (st != CP_OK || fits) return st;
+  return plan_items(large, 0, false, 0, out);
+}
 
 Layout layout_of(const Plan& plan) {
-  Layout l;
-  l.items = align_up(plan.descs.size() * sizeof(DevDesc));
-  l.splits = align_up(l.items + plan.items.size() * sizeof(WorkItem));
-  l.pieces = align_up(l.splits + plan.splits.size() * sizeof(SplitItem));
-  l.total = l.pieces + (size_t)plan.n_pieces * piece_bytes(plan.shape.rows_per_wg);
-  return l;
+  return layout_of_counts(plan.descs.size(), plan.items.size(), plan.splits.size(), (size_t)plan.n_pieces,
+                          plan.shape.rows_per_wg);
 }
 
 void pack_tables(const Plan& plan, const Layout& lay, unsigned char* host) {

@@ -227,10 +227,10 @@ struct Layout {
   size_t items, splits, pieces, total;
 };
 Layout layout_of(const Plan& plan);
-// The plan of a launch in `bytes` of workspace: when its piece slots do not
-// fit, fewer and longer pieces, down to none (the same attention, another
-// decomposition).  *lay is its layout, which exceeds `bytes` when not even the
-// tables fit; *wanted is the first plan's size.
+// The plan of a launch in `bytes` of workspace: where the free choice does not
+// fit, the fastest estimate among the lists of no more pieces that do (the same
+// attention, another decomposition).  *lay is its layout, which exceeds `bytes`
+// when not even the shortest tables fit; *wanted is the free choice's size.
 int build_plan_within(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv, size_t bytes, Plan* out,
                       Layout* lay, size_t* wanted);
 void pack_tables(const Plan& plan, const Layout& lay, unsigned char* host);
