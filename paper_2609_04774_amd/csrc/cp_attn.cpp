@@ -212,89 +212,129 @@ struct ItemTiles {
   int64_t tiles;  // its key walk
 };
 
-// Makespan of list scheduling `lens` (sorted longest first) onto units whose
-// loads start at `loads`.
-int64_t list_schedule(const std::vector<int64_t>& loads, const std::vector<int64_t>& lens) {
-  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> units(loads.begin(), loads.end());
-  int64_t makespan = *std::max_element(loads.begin(), loads.end());
-  for (int64_t len : lens) {
-    const int64_t t = units.top() + len + kItemSetupTiles;
-    units.pop();
-    units.push(t);
-    makespan = std::max(makespan, t);
+// The times at which one schedule's units fall free, as a binary heap: the root
+// is the first, and a unit that takes a workgroup sinks from there.
+template <class T>
+struct Units {
+  std::vector<T> free;
+  T end = 0;  // the makespan
+  explicit Units(int n) : free(n, T(0)) {}
+  void add(T len) {
+    const T t = free[0] + len;
+    const size_t n = free.size();
+    size_t i = 0;
+    for (size_t c = 1; c < n; c = 2 * i + 1) {
+      c += c + 1 < n && free[c + 1] < free[c];
+      if (free[c] >= t) break;
+      free[i] = free[c];
+      i = c;
+    }
+    free[i] = t;
+    end = std::max(end, t);
   }
-  return makespan;
+};
+
+// Makespan of list scheduling `lens` (sorted longest first) onto units whose
+// loads start at `loads`; or, as soon as it is known to exceed `give_up`,
+// something above that.
+int64_t list_schedule(const std::vector<int64_t>& loads, const std::vector<int64_t>& lens,
+                      int64_t give_up = INT64_MAX) {
+  // Of the r * n + 1 longest, some of n units takes r + 1: the shortest r + 1
+  // of them at least.
+  const size_t n = loads.size();
+  for (size_t r = 1; give_up != INT64_MAX && r * n < lens.size(); ++r) {
+    int64_t t = 0;
+    for (size_t i = r * n - r; i <= r * n; ++i) t += lens[i] + kItemSetupTiles;
+    if (t > give_up) return t;
+  }
+  Units<int64_t> units(0);
+  units.free = loads;
+  std::make_heap(units.free.begin(), units.free.end(), std::greater<int64_t>());
+  units.end = *std::max_element(loads.begin(), loads.end());
+  for (int64_t len : lens) {
+    units.add(len + kItemSetupTiles);
+    if (units.end > give_up) break;
+  }
+  return units.end;
 }
 
 typedef std::vector<std::vector<int32_t>> Cuts;  // per item (position in the list): cut points
 
-// The fill candidate (see balance_cuts), of at most max_pieces pieces.
-Cuts fill_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t ideal, int64_t limit, int64_t max_pieces) {
+// A way of cutting one schedule's items: where (position in the list, tile), the
+// lengths that result, and the lengths of the items left whole, longest first.
+struct Candidate {
+  std::vector<std::pair<size_t, int32_t>> cuts;
+  std::vector<int64_t> pieces, whole;
+};
+
+// The fill candidate (see balance_cuts), of at most max_pieces pieces.  `order`:
+// the items, longest first.
+Candidate fill_cuts(const std::vector<ItemTiles>& items, const std::vector<size_t>& order, int n_units, int64_t ideal,
+                    int64_t limit, int64_t max_pieces) {
   struct Seg {
     int64_t len;
     size_t idx;
     int32_t t0;
+    int n_cuts;  // of its item, so far
   };
-  Cuts c(items.size());
-  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> units;
-  for (int u = 0; u < n_units; ++u) units.push(0);
+  Candidate c;
+  Units<int64_t> units(n_units);
   auto longer = [](const Seg& a, const Seg& b) { return a.len < b.len || (a.len == b.len && a.idx > b.idx); };
-  std::priority_queue<Seg, std::vector<Seg>, decltype(longer)> queue(longer);
-  for (size_t i = 0; i < items.size(); ++i) queue.push(Seg{items[i].tiles, i, 0});
-  int64_t pieces = 0;
-  while (!queue.empty()) {
-    const Seg s = queue.top();
-    queue.pop();
-    const int64_t load = units.top();
-    units.pop();
+  std::priority_queue<Seg, std::vector<Seg>, decltype(longer)> rest(longer);  // what cuts left
+  int64_t n_pieces = 0;
+  for (size_t next = 0; next < order.size() || !rest.empty();) {
+    Seg s{0, 0, 0, 0};
+    if (next < order.size()) s = Seg{items[order[next]].tiles, order[next], 0, 0};
+    if (next == order.size() || (!rest.empty() && longer(s, rest.top()))) {
+      s = rest.top();
+      rest.pop();
+    } else {
+      ++next;
+    }
+    const int64_t load = units.free[0];
     int64_t take = s.len;
-    const int64_t more = c[s.idx].empty() ? 2 : 1;  // pieces that a cut here adds
-    if (load + s.len + kItemSetupTiles > limit && (int64_t)c[s.idx].size() + 1 < kMaxPieces &&
-        pieces + more <= max_pieces) {
+    const int64_t more = s.n_cuts == 0 ? 2 : 1;  // pieces that a cut here adds
+    if (load + s.len + kItemSetupTiles > limit && s.n_cuts + 1 < kMaxPieces && n_pieces + more <= max_pieces) {
       // Fill this unit up to the ideal, or give it the smallest piece when
       // it is there already.
       const int64_t room = ideal - load - kItemSetupTiles;
       if (s.len >= 2 * kMinBalancePiece) take = std::min(std::max(room, kMinBalancePiece), s.len - kMinBalancePiece);
     }
-    units.push(load + take + kItemSetupTiles);
+    units.add(take + kItemSetupTiles);
+    (s.n_cuts == 0 && take == s.len ? c.whole : c.pieces).push_back(take);
     if (take < s.len) {
-      pieces += more;
-      c[s.idx].push_back(s.t0 + (int32_t)take);
-      queue.push(Seg{s.len - take, s.idx, s.t0 + (int32_t)take});
+      n_pieces += more;
+      c.cuts.push_back(std::make_pair(s.idx, s.t0 + (int32_t)take));
+      rest.push(Seg{s.len - take, s.idx, s.t0 + (int32_t)take, s.n_cuts + 1});
     }
   }
-  for (std::vector<int32_t>& v : c) std::sort(v.begin(), v.end());
   return c;
 }
 
-// The even candidate for m units' worth of pieces (see balance_cuts); no cut
-// when it makes none.
-Cuts even_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t limit, int m) {
-  Cuts c(items.size());
-  std::vector<size_t> order(items.size());
-  for (size_t i = 0; i < items.size(); ++i) order[i] = i;
-  std::sort(order.begin(), order.end(), [&](size_t a, size_t b) {
-    return items[a].tiles > items[b].tiles || (items[a].tiles == items[b].tiles && a < b);
-  });
-  // The longest items, each while the least loaded unit takes it within the
-  // limit.
-  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> units;
-  for (int u = 0; u < n_units; ++u) units.push(0);
-  size_t n_whole = 0;
-  for (; n_whole < order.size(); ++n_whole) {
-    const int64_t t = units.top() + items[order[n_whole]].tiles + kItemSetupTiles;
-    if (t > limit) break;
-    units.pop();
-    units.push(t);
+// How many of the items (longest first) are placed whole, each while the least
+// loaded unit takes it within the limit.
+size_t placed_whole(const std::vector<ItemTiles>& items, const std::vector<size_t>& order, int n_units, int64_t limit) {
+  Units<int64_t> units(n_units);
+  size_t n = 0;
+  for (; n < order.size(); ++n) {
+    const int64_t len = items[order[n]].tiles + kItemSetupTiles;
+    if (units.free[0] + len > limit) break;
+    units.add(len);
   }
-  std::vector<size_t> big;  // the rest that can be cut in two
+  return n;
+}
+
+// The even candidate (see balance_cuts) of `target` pieces of the items that can
+// be cut in two, beyond the first n_whole; no cut when it makes none.
+Candidate even_cuts(const std::vector<ItemTiles>& items, const std::vector<size_t>& order, size_t n_whole,
+                    int64_t target) {
+  Candidate c;
+  std::vector<size_t> big;
   int64_t big_tiles = 0;
-  for (size_t k = n_whole; k < order.size(); ++k)
-    if (items[order[k]].tiles >= 2 * kMinBalancePiece) {
-      big.push_back(order[k]);
-      big_tiles += items[order[k]].tiles;
-    }
-  const int64_t target = (int64_t)m * n_units;
+  for (size_t k = n_whole; k < order.size() && items[order[k]].tiles >= 2 * kMinBalancePiece; ++k) {
+    big.push_back(order[k]);
+    big_tiles += items[order[k]].tiles;
+  }
   if (target <= (int64_t)big.size()) return c;
   // Pieces in proportion to the lengths (largest remainders first), each
   // item's at most its length allows.
@@ -313,28 +353,18 @@ Cuts even_cuts(const std::vector<ItemTiles>& items, int n_units, int64_t limit, 
     return x.first > y.first;
   });
   for (size_t f = 0; f < frac.size() && dealt < target; ++f, ++dealt) ++n_pieces[frac[f].second];
-  for (size_t i = 0; i < big.size(); ++i) {
-    const int64_t len = items[big[i]].tiles;
-    for (int64_t k = 1; k < n_pieces[i]; ++k) c[big[i]].push_back((int32_t)(len * k / n_pieces[i]));
+  for (size_t k = 0; k < order.size(); ++k) {
+    const int64_t len = items[order[k]].tiles;
+    const int64_t n = k >= n_whole && k - n_whole < big.size() ? n_pieces[k - n_whole] : 1;
+    if (n == 1) c.whole.push_back(len);
+    for (int64_t j = 1, prev = 0; n > 1 && j <= n; ++j) {
+      const int64_t at = len * j / n;
+      c.pieces.push_back(at - prev);
+      if (j < n) c.cuts.push_back(std::make_pair(order[k], (int32_t)at));
+      prev = at;
+    }
   }
   return c;
-}
-
-// The dispatch's schedule of a candidate: makespan and piece count.
-std::pair<int64_t, int64_t> score_cuts(const std::vector<ItemTiles>& items, const Cuts& c, int n_units) {
-  std::vector<int64_t> lens;
-  int64_t pieces = 0;
-  for (size_t i = 0; i < items.size(); ++i) {
-    int32_t prev = 0;
-    for (int32_t x : c[i]) {
-      lens.push_back(x - prev);
-      prev = x;
-    }
-    lens.push_back(items[i].tiles - prev);
-    if (!c[i].empty()) pieces += (int64_t)c[i].size() + 1;
-  }
-  std::sort(lens.begin(), lens.end(), std::greater<int64_t>());
-  return std::make_pair(list_schedule(std::vector<int64_t>(n_units, 0), lens), pieces);
 }
 
 void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_items_total, int64_t max_pieces, Cuts* cuts) {
@@ -349,26 +379,36 @@ void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_ite
   // List scheduling ends within one item of the even spread: when the longest
   // item fits in the slack, no schedule needs cuts (and none is simulated).
   if (ideal + longest + kItemSetupTiles <= limit) return;
-  const Cuts none(items.size());
-  std::pair<int64_t, int64_t> best = score_cuts(items, none, n_units);
+  std::vector<size_t> order(items.size());  // longest first
+  std::iota(order.begin(), order.end(), (size_t)0);
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return items[a].tiles > items[b].tiles; });
+  const std::vector<int64_t> idle(n_units, 0);
+  std::vector<int64_t> lens;
+  for (size_t i : order) lens.push_back(items[i].tiles);
+  // The best makespan and its piece count.
+  std::pair<int64_t, int64_t> best(list_schedule(idle, lens), 0);
   if (best.first <= limit) return;
-  Cuts chosen;
-  auto consider = [&](Cuts c) {
-    const std::pair<int64_t, int64_t> sc = score_cuts(items, c, n_units);
-    if (sc.second > max_pieces) return;
-    if (sc.first < best.first || (sc.first == best.first && sc.second < best.second)) {
+  Candidate chosen;
+  auto consider = [&](Candidate c) {
+    const int64_t n_pieces = (int64_t)c.pieces.size();
+    const int64_t n_cuts = n_pieces + (int64_t)c.whole.size() - (int64_t)items.size();
+    if (n_pieces == 0 || n_pieces > max_pieces || (total + n_cuts * kItemSetupTiles) / n_units > best.first) return;
+    std::sort(c.pieces.begin(), c.pieces.end(), std::greater<int64_t>());
+    lens.resize(c.pieces.size() + c.whole.size());
+    std::merge(c.pieces.begin(), c.pieces.end(), c.whole.begin(), c.whole.end(), lens.begin(), std::greater<int64_t>());
+    const std::pair<int64_t, int64_t> sc(list_schedule(idle, lens, best.first), n_pieces);
+    if (sc < best) {
       best = sc;
-      chosen.swap(c);
+      chosen = std::move(c);
     }
   };
-  consider(fill_cuts(items, n_units, ideal, limit, max_pieces));
-  for (int m = 1; m <= 4; ++m) consider(even_cuts(items, n_units, limit, m));
-  if (chosen.empty()) return;
-  for (size_t i = 0; i < items.size(); ++i) {
-    if (chosen[i].empty()) continue;
-    if (cuts->empty()) cuts->resize(n_items_total);
-    (*cuts)[(size_t)items[i].item] = chosen[i];
-  }
+  consider(fill_cuts(items, order, n_units, ideal, limit, max_pieces));
+  const size_t n_whole = placed_whole(items, order, n_units, limit);
+  for (int m = 1; m <= 4; ++m) consider(even_cuts(items, order, n_whole, (int64_t)m * n_units));
+  if (chosen.cuts.empty()) return;
+  cuts->resize(n_items_total);
+  for (const std::pair<size_t, int32_t>& c : chosen.cuts) (*cuts)[(size_t)items[c.first].item].push_back(c.second);
+  for (const ItemTiles& it : items) std::sort((*cuts)[(size_t)it.item].begin(), (*cuts)[(size_t)it.item].end());
 }
 
 // Key tiles of one work item's walk, exactly as the kernel counts them: the
@@ -468,15 +508,16 @@ int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap
     const int64_t len = std::max<int64_t>(kPinnedMinTiles, (b_.all_tiles + target_pieces - 1) / target_pieces);
     cut_all([&](int64_t tiles) { return std::min<int64_t>(kMaxPieces, tiles / len); });
   } else if (target_pieces > 0) {
+    // The first schedule's items; the others' are those of the next head groups.
     const int n_sched = schedules_of(n_groups);
     std::vector<ItemTiles> sched;
-    for (int x = 0; x < n_sched; ++x) {
-      sched.clear();
-      for (size_t bi = 0; bi < blocks.size(); ++bi)
-        if (blocks[bi].tiles > 0)
-          for (int g = x; g < n_groups; g += n_sched) sched.push_back(ItemTiles{(int64_t)(bi * n_groups + g), blocks[bi].tiles});
-      balance_cuts(sched, kComputeUnits / n_sched, blocks.size() * n_groups, max_pieces / n_sched, &cuts);
-    }
+    for (size_t bi = 0; bi < blocks.size(); ++bi)
+      if (blocks[bi].tiles > 0)
+        for (int g = 0; g < n_groups; g += n_sched) sched.push_back(ItemTiles{(int64_t)(bi * n_groups + g), blocks[bi].tiles});
+    balance_cuts(sched, kComputeUnits / n_sched, blocks.size() * n_groups, max_pieces / n_sched, &cuts);
+    if (!cuts.empty())
+      for (const ItemTiles& it : sched)
+        for (int x = 1; x < n_sched; ++x) cuts[(size_t)it.item + x] = cuts[(size_t)it.item];
   }
   out->splits.clear();
   out->n_pieces = 0;
@@ -549,45 +590,21 @@ double merge_us(const Shape& s, int64_t n_pieces, int64_t n_splits) {
   return kMergeUs + (double)piece_bytes(s.rows_per_wg) * (2.0 * n_pieces + n_splits) / kMergeBytesPerUs;
 }
 
-// One schedule's units: a binary heap of the times they fall free at (the
-// root is the first; a unit that takes a workgroup sinks from there), the
-// makespan and the time they are busy in all.
-struct Units {
-  std::vector<double> free;
-  double end = 0.0, sum = 0.0;
-  explicit Units(int n) : free(n, 0.0) {}
-  void add(double us) {
-    const double t = free[0] + us;
-    const size_t n = free.size();
-    size_t i = 0;
-    for (size_t c = 1; c < n; c = 2 * i + 1) {
-      c += c + 1 < n && free[c + 1] < free[c];
-      if (free[c] >= t) break;
-      free[i] = free[c];
-      i = c;
-    }
-    free[i] = t;
-    end = std::max(end, t);
-    sum += us;
-  }
-};
-
 double slowed(double end, double sum, int n_units) { return end > 0.0 ? end + kBusySlowdown * sum / n_units : 0.0; }
 
 double estimate_us(const Plan& plan) {
   const double tile = tile_us(plan.shape);
-  std::vector<Units> units(kXcds, Units(kComputeUnits / kXcds));
+  std::vector<Units<double>> units(kXcds, Units<double>(kComputeUnits / kXcds));
+  double sum = 0.0;
   for (size_t i = 0; i < plan.items.size(); ++i) {
     const WorkItem& w = plan.items[i];
     const int64_t tiles = w.t_end >= 0 ? (int64_t)(w.t_end - w.t_begin)
                                        : item_tiles(plan.descs[w.desc], w.chunk, w.q_block, plan.shape.q_per_wg);
     units[i % kXcds].add(tiles * tile + kItemSetupUs);
+    sum += tiles * tile + kItemSetupUs;
   }
-  double end = 0.0, sum = 0.0;
-  for (const Units& u : units) {
-    end = std::max(end, u.end);
-    sum += u.sum;
-  }
+  double end = 0.0;
+  for (const Units<double>& u : units) end = std::max(end, u.end);
   return slowed(end, sum, kComputeUnits) + merge_us(plan.shape, plan.n_pieces, (int64_t)plan.splits.size());
 }
 
@@ -603,79 +620,85 @@ Layout layout_of_counts(size_t n_descs, size_t n_items, size_t n_splits, size_t 
   return l;
 }
 
-// A candidate list of one shape: its walks cut to `cap` tiles, its estimate,
-// the bytes of its piece slots and of its workspace.
+// A candidate list of one shape: its walks cut to `cap` tiles, its workspace,
+// its estimate and a bound below it: its work spread evenly over the units (or
+// its longest piece alone), and its merge.
 struct Choice {
   const Blocks* blocks;
-  int64_t cap;
-  double us;
-  size_t slots, total;
+  int64_t cap, n_pieces, n_splits;
+  size_t total;
+  double at_least, us;
+  size_t slots() const { return (size_t)n_pieces * piece_bytes(blocks->shape.rows_per_wg); }
 };
 
-// The same estimate for a list cut to `cap` tiles, without building it.
-// `lens` is scratch (length, count).
-Choice estimate_cap(const Blocks& b, int64_t cap, std::vector<std::pair<int64_t, int64_t>>* lens) {
+// The same estimate for a list cut to c.cap tiles, without building it; or, as
+// soon as it is known to exceed `give_up`, something above that.  `lens` is
+// scratch (length, count).
+double estimate_cap(const Choice& c, double give_up, std::vector<std::pair<int64_t, int64_t>>* lens) {
+  const Blocks& b = *c.blocks;
   const int n_sched = schedules_of(b.n_groups), per_sched = b.n_groups / n_sched;
   lens->clear();
-  int64_t n_pieces = 0, n_splits = 0;
+  int64_t n_items = 0;
   for (const Block& x : b.list) {
     // Equal parts: x.tiles % n of them are one tile longer than the others.
-    const int64_t n = pieces_at(x.tiles, cap), longer = x.tiles % n;
+    const int64_t n = pieces_at(x.tiles, c.cap), longer = x.tiles % n;
     if (longer) lens->push_back(std::make_pair(x.tiles / n + 1, longer * per_sched));
     lens->push_back(std::make_pair(x.tiles / n, (n - longer) * per_sched));
-    if (n > 1) {
-      n_pieces += n * b.n_groups;
-      n_splits += b.n_groups;
-    }
+    n_items += n * per_sched;
   }
   std::sort(lens->begin(), lens->end(), std::greater<std::pair<int64_t, int64_t>>());
   const int n_units = kComputeUnits / n_sched;
-  Units units(n_units);
-  for (const std::pair<int64_t, int64_t>& len : *lens)
-    for (int64_t i = 0; i < len.second; ++i) units.add(len.first * tile_us(b.shape) + kItemSetupUs);
-  Choice c;
-  c.blocks = &b;
-  c.cap = cap;
-  c.us = slowed(units.end, units.sum, n_units) + merge_us(b.shape, n_pieces, n_splits);
-  c.slots = (size_t)n_pieces * piece_bytes(b.shape.rows_per_wg);
-  c.total = 0;
-  return c;
+  const double rest = kBusySlowdown * (b.all_tiles / n_sched * tile_us(b.shape) + n_items * kItemSetupUs) / n_units +
+                      merge_us(b.shape, c.n_pieces, c.n_splits);
+  // As in list_schedule: of the r * n + 1 longest, some unit takes r + 1, no
+  // shorter than the last of them.
+  int64_t before = 0;
+  for (const std::pair<int64_t, int64_t>& len : *lens) {
+    before += len.second;
+    const double us = len.first * tile_us(b.shape) + kItemSetupUs;
+    if ((double)((before - 1) / n_units + 1) * us + rest > give_up) return INFINITY;
+  }
+  Units<double> units(n_units);
+  for (const std::pair<int64_t, int64_t>& len : *lens) {
+    const double us = len.first * tile_us(b.shape) + kItemSetupUs;
+    for (int64_t i = 0; i < len.second; ++i) units.add(us);
+    if (units.end + rest > give_up) break;
+  }
+  return units.end > 0.0 ? units.end + rest : 0.0;
 }
 
-// Adds one shape's candidates: the longest walk cut into k = 1, 2, ... equal
-// pieces and every other walk to that length.  Once the even spread of a cut
-// list over the units, and its merge, alone end after the best candidate
-// (*best), or its workspace exceeds `limit`, more pieces only add to them: there
-// the search stops.
-void add_choices(const Blocks& b, size_t n_descs, int64_t target_pieces, size_t limit, double* best,
-                 std::vector<Choice>* out) {
-  std::vector<std::pair<int64_t, int64_t>> lens;
+// Adds one shape's candidates (not yet estimated): the longest walk cut into k =
+// 1, 2, ... equal pieces and every other walk to that length, while their
+// pieces and workspace stay within the limits.
+void add_choices(const Blocks& b, size_t n_descs, int64_t target_pieces, size_t limit, std::vector<Choice>* out) {
   int64_t last = 0;
   for (int64_t k = 1; k <= kMaxPieces; ++k) {
     const int64_t cap = std::max<int64_t>(1, (b.max_tiles + k - 1) / k);
     if (k > 1 && (cap < kMinPieceTiles || target_pieces == 0)) break;
     if (cap == last) continue;
     last = cap;
-    int64_t n = 0, n_pieces = 0, n_splits = 0, shortest = b.max_tiles;
+    Choice c{&b, cap, 0, 0, 0, 0.0, INFINITY};
+    int64_t n = 0, shortest = b.max_tiles, longest = 0;
     for (const Block& x : b.list) {
       const int64_t m = pieces_at(x.tiles, cap);
       n += m;
+      longest = std::max(longest, (x.tiles + m - 1) / m);
       if (m > 1) {
-        n_pieces += m;
-        ++n_splits;
+        c.n_pieces += m;
+        ++c.n_splits;
         shortest = std::min(shortest, x.tiles / m);
       }
     }
     n *= b.n_groups;
-    n_pieces *= b.n_groups;
-    const size_t total = layout_of_counts(n_descs, n, n_splits * b.n_groups, n_pieces, b.shape.rows_per_wg).total;
-    if (total > limit) break;
-    if (k > 1 && (n_pieces > target_pieces || shortest < kMinPieceTiles)) break;
+    c.n_pieces *= b.n_groups;
+    c.n_splits *= b.n_groups;
+    c.total = layout_of_counts(n_descs, n, c.n_splits, c.n_pieces, b.shape.rows_per_wg).total;
+    if (c.total > limit || (k > 1 && (c.n_pieces > target_pieces || shortest < kMinPieceTiles))) break;
     const double spread = (b.all_tiles * tile_us(b.shape) + n * kItemSetupUs) / kComputeUnits;
-    if (k > 1 && slowed(spread, spread, 1) + merge_us(b.shape, n_pieces, 1) >= *best) break;
-    out->push_back(estimate_cap(b, cap, &lens));
-    out->back().total = total;
-    *best = std::min(*best, out->back().us);
+    const double alone = longest * tile_us(b.shape) + kItemSetupUs;
+    if (n > 0)
+      c.at_least = std::max(spread, alone) + kBusySlowdown * spread + merge_us(b.shape, c.n_pieces, c.n_splits);
+    out->push_back(c);
   }
 }
 
@@ -831,24 +854,36 @@ static int choose_list(const Blocks& small, const Blocks& large, const Blocks* w
     if (st != CP_OK || *fits) return st;
   }
   std::vector<Choice> choices;
-  double best_us = INFINITY;
-  add_choices(small, n_descs, std::min(target_pieces, max_pieces), limit, &best_us, &choices);
-  add_choices(large, n_descs, std::min(target_pieces, max_pieces), limit, &best_us, &choices);
+  add_choices(small, n_descs, std::min(target_pieces, max_pieces), limit, &choices);
+  add_choices(large, n_descs, std::min(target_pieces, max_pieces), limit, &choices);
   *fits = !choices.empty();
   if (!*fits) return CP_OK;
-  const Choice* best = &choices[0];
-  for (const Choice& c : choices)
-    if (c.us < best->us) best = &c;
   // Piece slots that fit the eight 4 MB L2s, and with the tables the scratch
   // of cp_attn_partial_noalloc (then both entry points run the same list),
   // are worth a few per cent: 300 rows after 16K cached keys ran 108.4 us in
   // 240 slots of 256 rows (32 MB) against 108.2 in 256 of 384 (51 MB).
   constexpr size_t kSlotBytes = (size_t)(32 << 20) - (256 << 10);
   constexpr double kSlotGain = 1.04;
-  if (best->slots > kSlotBytes) {
+  // Estimated in the order of their bounds; most of them are settled by that.
+  std::vector<Choice*> order;
+  for (Choice& c : choices) order.push_back(&c);
+  std::stable_sort(order.begin(), order.end(), [](const Choice* a, const Choice* b) { return a->at_least < b->at_least; });
+  std::vector<std::pair<int64_t, int64_t>> lens;
+  double best_us = INFINITY;
+  for (Choice* c : order) {
+    // Rounding aside, no estimate is below its bound.
+    const double give_up = (c->slots() <= kSlotBytes ? kSlotGain : 1.0) * best_us * (1.0 + 1e-9);
+    if (c->at_least > give_up) continue;
+    c->us = estimate_cap(*c, give_up, &lens);
+    best_us = std::min(best_us, c->us);
+  }
+  const Choice* best = &choices[0];
+  for (const Choice& c : choices)
+    if (c.us < best->us) best = &c;
+  if (best->slots() > kSlotBytes) {
     const Choice* within = nullptr;
     for (const Choice& c : choices)
-      if (c.slots <= kSlotBytes && (!within || c.us < within->us)) within = &c;
+      if (c.slots() <= kSlotBytes && (!within || c.us < within->us)) within = &c;
     if (within && within->us <= kSlotGain * best->us) best = within;
   }
   const Choice chosen = *best;
@@ -858,6 +893,8 @@ static int choose_list(const Blocks& small, const Blocks& large, const Blocks* w
   double us = chosen.us;
   for (const Blocks* b : {&small, &large}) {
     if (b->max_tiles < 2 * kMinBalancePiece) continue;
+    const double spread = shape_bounds(*b).lo;
+    if (slowed(spread, spread, 1) >= us) continue;  // no list of this shape ends sooner
     Plan balanced;
     balanced.descs = out->descs;
     const int st2 = balance(*b, &balanced);
