@@ -550,15 +550,28 @@ int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap
   out->items.clear();
   out->items.reserve((size_t)total);
   std::vector<size_t> head(kXcds, 0);
+  std::vector<int> from(kXcds);  // an XCD's list, and later the one it took from last
+  std::iota(from.begin(), from.end(), 0);
   for (int64_t i = 0; i < total; ++i) {
-    int x = (int)(i % kXcds);
-    if (head[x] == per_xcd[x].size()) {
-      // This XCD's list ran dry: take the costliest remaining item anywhere.
-      int best = -1;
-      for (int y = 0; y < kXcds; ++y)
-        if (head[y] < per_xcd[y].size() && (best < 0 || per_xcd[y][head[y]].cost > per_xcd[best][head[best]].cost))
-          best = y;
-      x = best;
+    // The list that this XCD took from last while its next item is as long as
+    // any that is left (always, where the lists are alike: the groups a multiple
+    // of the XCDs); else, of the lists with such an item, the one with the most
+    // left.  The launch as a whole is then dispatched longest first, as its choice
+    // supposes: where XCDs took their own list's shorter items first, long ones
+    // were left for the end.
+    int& x = from[i % kXcds];
+    int64_t top = -1;
+    for (int y = 0; y < kXcds; ++y)
+      if (head[y] < per_xcd[y].size()) top = std::max(top, per_xcd[y][head[y]].cost);
+    if (head[x] == per_xcd[x].size() || per_xcd[x][head[x]].cost < top) {
+      size_t most = 0;
+      for (int y = 0; y < kXcds; ++y) {
+        const size_t left = per_xcd[y].size() - head[y];
+        if (left > most && per_xcd[y][head[y]].cost == top) {
+          most = left;
+          x = y;
+        }
+      }
     }
     out->items.push_back(per_xcd[x][head[x]++].w);
   }

@@ -9,6 +9,8 @@
 //   * pieces keep the minimum sizes of their policy (at least 32 tiles when a
 //     launch with few items is split for occupancy, 256 for balance cuts,
 //     whether they fill units up or cut items evenly);
+//   * the launch is dispatched longest first; with head groups a multiple of
+//     the XCDs, every group's items land on one XCD;
 //   * the work list holds nothing else, and the workspace layout holds one
 //     slot of the shape's size per piece;
 //   * a launch planned again is served from the plan cache with the list a
@@ -111,6 +113,16 @@ void check(const Launch& l, int rows) {
       t = slot_range[p].second;
     }
     expect(expected.count(k) && t == expected[k], who + ": pieces do not end at the walk's end");
+  }
+  int64_t previous = INT64_MAX;
+  for (size_t i = 0; i < plan.items.size(); ++i) {
+    const WorkItem& w = plan.items[i];
+    const int64_t cost = w.piece >= 0 ? (int64_t)(w.t_end - w.t_begin) * 32
+                                      : item_keys(plan.descs[w.desc], w.chunk, w.q_block, sh.q_per_wg);
+    if (n_groups % kXcds == 0)
+      expect(w.head_group % kXcds == (int)(i % kXcds), who + ": item on another XCD than its group's");
+    expect(cost <= previous, who + ": a longer item after a shorter one");
+    previous = cost;
   }
   for (const auto& e : expected) {
     const bool is_whole = whole.count(e.first) != 0, is_split = split_of.count(e.first) != 0;
