@@ -48,7 +48,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // kLanes lanes copy one row of kSets tensors: lane l moves 16-byte pieces l,
 // l + kLanes, ...  A null source writes zeros.
 // kStream: loads with the non-temporal hint.
-template <int kLanes, int kSets, bool kStream = true>
+template <int kLanes, int kSets, bool kStream>
 __device__ __forceinline__ void copy_rows(const unsigned char* const (&src)[kSets], unsigned char* const (&dst)[kSets],
                                           int64_t row_bytes, int lane) {
   const int64_t n = row_bytes >> 4;
@@ -118,13 +118,13 @@ __device__ __forceinline__ RankRow rank_row(int64_t i, int64_t C, int64_t s, int
 
 // One destination rank: each of its rows fetched from where it sits at the
 // source degree.
-template <int kLanes>
+template <int kLanes, bool kStream>
 __global__ __launch_bounds__(kThreads) void repartition_kernel(RepartitionParams p) {
   const int64_t t = row_index<kLanes>();
   if (t >= p.n_rows) return;
   const RankRow from = rank_row(row_position(p.dst_q_begin, p.dst_q_len, t) - p.P, p.C_src, p.s_src, p.R);
-  copy_rows<kLanes, 1>({p.src[from.rank] + from.row * p.row_bytes}, {p.dst + t * p.row_bytes}, p.row_bytes,
-                       threadIdx.x % kLanes);
+  copy_rows<kLanes, 1, kStream>({p.src[from.rank] + from.row * p.row_bytes}, {p.dst + t * p.row_bytes}, p.row_bytes,
+                                threadIdx.x % kLanes);
 }
 
 // Every row of the suffix from its source rank to its destination rank, in
@@ -154,8 +154,9 @@ __global__ __launch_bounds__(kThreads) void kv_gather_kernel(GatherParams p) {
   const int64_t blk = p.block_table[pos / kBlockTokens];
   const bool inside = blk >= 0 && blk < p.n_blocks;
   const int64_t src = (blk * kBlockTokens + pos % kBlockTokens) * p.row_bytes;
-  copy_rows<kLanes, 2>({inside ? p.k_cache + src : nullptr, inside ? p.v_cache + src : nullptr},
-                       {p.k_rows + t * p.row_bytes, p.v_rows + t * p.row_bytes}, p.row_bytes, threadIdx.x % kLanes);
+  copy_rows<kLanes, 2, true>({inside ? p.k_cache + src : nullptr, inside ? p.v_cache + src : nullptr},
+                             {p.k_rows + t * p.row_bytes, p.v_rows + t * p.row_bytes}, p.row_bytes,
+                             threadIdx.x % kLanes);
 }
 
 // Launches the kernel of the fewest lanes that hold a row's pieces one each.
@@ -205,8 +206,11 @@ int launch_writeback(const WritebackParams& p, void* stream) {
 }
 
 int launch_repartition(const RepartitionParams& p, void* stream) {
-  return launch_rows(repartition_kernel<16>, repartition_kernel<32>, repartition_kernel<64>, p, p.n_rows,
-                     "cp_repartition", stream);
+  if (p.n_rows * p.row_bytes > kInfinityCacheBytes)
+    return launch_rows(repartition_kernel<16, true>, repartition_kernel<32, true>, repartition_kernel<64, true>, p,
+                       p.n_rows, "cp_repartition", stream);
+  return launch_rows(repartition_kernel<16, false>, repartition_kernel<32, false>, repartition_kernel<64, false>, p,
+                     p.n_rows, "cp_repartition", stream);
 }
 
 }  // namespace cpattn

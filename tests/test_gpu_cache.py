@@ -324,3 +324,5 @@ def test_copies_on_both_sides_of_the_infinity_cache(R):
     cp.repartition_all(0, n, [[one]], [parts])
     cp.repartition_all(0, n, [parts], [[back]])
     assert torch.equal(one.view(torch.int16), back.view(torch.int16))
+    cp.repartition(0, n, parts, 1, 0, back.zero_())
+    assert torch.equal(one.view(torch.int16), back.view(torch.int16))
