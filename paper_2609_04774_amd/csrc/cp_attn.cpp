@@ -160,9 +160,10 @@ int to_dev(const cp_partial_desc& x, int idx, DevDesc* out) {
 // The last rank's chunks (C-1 and C; both of a degree of 1) follow one another,
 // in the sequence and in the rank's rows: as one chunk they end in one ragged
 // query block instead of two.  300 rows of 32 heads on 8 KV heads, behind 16K
-// cached tokens, are 5 blocks of 64 positions, not 6: 102.6 -> 94.9 us; a batch
-// of 64 requests, 58 of degree 1, 10635 -> 10505.  (Not with a pinned workgroup
-// shape, whose lists keep one fixed rule.)
+// cached tokens, are 5 blocks of 64 positions, not 6: 103.1 -> 95.4 us.  (A batch
+// of 64 requests, 58 of degree 1, 10835 -> 10761, is within its spread of 2 %.)
+// Not with a pinned workgroup shape, whose lists keep one fixed rule, nor where
+// the launch is uncut and within one round without it (plan_joined).
 void join_chunks(DevDesc* d) {
   if (d->q_len[1] == 0 || d->q_begin[1] != d->q_begin[0] + d->q_len[0] ||
       d->local_off[1] != d->local_off[0] + d->q_len[0] || d->o_off[1] != d->o_off[0] + d->q_len[0])
@@ -762,6 +763,7 @@ struct CachedPlan {
   std::vector<SplitItem> splits;
   int64_t n_pieces;
   Shape shape;
+  bool joined;  // of the joined descriptors
   size_t total, limit, wanted;
 };
 constexpr size_t kPlanCacheSize = 16;
@@ -784,6 +786,43 @@ static std::vector<int64_t> plan_key(const std::vector<DevDesc>& descs, int32_t 
 static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out,
                          size_t limit = SIZE_MAX, size_t* wanted = nullptr);
 
+// The plan of a launch's joined descriptors (*joined), or of the descriptors as
+// they are where that is one round of uncut items: there idle compute units
+// take the second chunk's rows sooner than the first chunk's workgroups (80 rows
+// of 32 heads on 8, without a prefix: 8.1-8.6 us of kernel joined, 7.1 not).
+static int plan_joined(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out, size_t limit,
+                       size_t* wanted, bool* joined) {
+  Plan apart;
+  apart.descs = out->descs;
+  *joined = false;
+  if (forced == 0)
+    for (size_t i = 0; i < out->descs.size(); ++i) {
+      join_chunks(&out->descs[i]);
+      *joined |= out->descs[i].q_len[1] != apart.descs[i].q_len[1];
+    }
+  if (!*joined) return plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, wanted);
+  Plan free_choice;
+  free_choice.descs = out->descs;
+  int st = plan_uncached(Hq, Hkv, target_pieces, forced, &free_choice, SIZE_MAX, wanted);
+  if (st != CP_OK) return st;
+  auto one_round = [](const Plan& p) { return p.n_pieces == 0 && p.items.size() <= (size_t)kComputeUnits; };
+  bool apart_chosen = false;
+  if (one_round(free_choice)) {
+    size_t size = 0;
+    st = plan_uncached(Hq, Hkv, target_pieces, forced, &apart, SIZE_MAX, &size);
+    if (st != CP_OK) return st;
+    apart_chosen = one_round(apart);
+    if (apart_chosen) *wanted = size;
+  }
+  if (*wanted > limit) {
+    size_t size = 0;
+    return plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, &size);
+  }
+  *out = apart_chosen ? std::move(apart) : std::move(free_choice);
+  *joined = !apart_chosen;
+  return CP_OK;
+}
+
 // The plan of a launch in `limit` bytes of workspace; *wanted is the size of
 // the unlimited one.
 static int build_plan_limited(const cp_partial_desc* descs, int32_t n_descs, int32_t Hq, int32_t Hkv,
@@ -798,8 +837,6 @@ static int build_plan_limited(const cp_partial_desc* descs, int32_t n_descs, int
     if (st != CP_OK) return st;
   }
   const int forced = g_forced_rows.load();
-  if (forced == 0)
-    for (DevDesc& d : out->descs) join_chunks(&d);
   std::vector<int64_t> key = plan_key(out->descs, Hq, Hkv, target_pieces, forced);
   {
     std::lock_guard<std::mutex> lock(g_plan_cache_mu);
@@ -810,12 +847,15 @@ static int build_plan_limited(const cp_partial_desc* descs, int32_t n_descs, int
       out->splits = c.splits;
       out->n_pieces = c.n_pieces;
       out->shape = c.shape;
+      if (c.joined)
+        for (DevDesc& d : out->descs) join_chunks(&d);
       *wanted = c.wanted;
       ++g_plan_cache_hits;
       return CP_OK;
     }
   }
-  st = plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, wanted);
+  bool joined = false;
+  st = plan_joined(Hq, Hkv, target_pieces, forced, out, limit, wanted, &joined);
   if (st != CP_OK) return st;
   const size_t total = layout_of(*out).total;
   if (total > limit) return CP_OK;  // the caller refuses it
@@ -823,7 +863,7 @@ static int build_plan_limited(const cp_partial_desc* descs, int32_t n_descs, int
   std::lock_guard<std::mutex> lock(g_plan_cache_mu);
   if (g_plan_cache.size() == kPlanCacheSize) g_plan_cache.erase(g_plan_cache.begin());
   g_plan_cache.push_back(
-      CachedPlan{std::move(key), out->items, out->splits, out->n_pieces, out->shape, total, limit, *wanted});
+      CachedPlan{std::move(key), out->items, out->splits, out->n_pieces, out->shape, joined, total, limit, *wanted});
   return CP_OK;
 }
 

@@ -254,6 +254,15 @@ int main() {
     expect(other.shape.rows_per_wg == kRowsSmall, "plan cache: the pinned shape was not planned");
     cp_set_workgroup_rows(0);
   }
+  // The last rank's adjacent chunks are one, from the planner and from the
+  // cache, except where both are within one round of uncut items.
+  for (int again = 0; again < 2; ++again) {
+    const cp_partial_desc turn = desc(16368, 300, 1, 0, CP_KV_ALL, 1), small = desc(0, 160, 2, 1, CP_KV_ALL, 1);
+    build_plan(&turn, 1, 32, 8, kTargetPieces, &p);
+    expect(p.descs[0].q_len[0] == 300 && p.descs[0].q_len[1] == 0, "chunks of a cut launch apart");
+    build_plan(&small, 1, 32, 8, kTargetPieces, &p);
+    expect(p.descs[0].q_len[0] == 40 && p.descs[0].q_len[1] == 40 && p.n_pieces == 0, "chunks of one uncut round joined");
+  }
   // The per-launch choice keeps 384 rows for that launch and 256 for few
   // long walks.
   cp_set_workgroup_rows(0);
