@@ -63,9 +63,9 @@ def parse():
     ap.add_argument("--cpu-seconds", type=float, default=12.0,
                     help="wall-clock budget of the CPU oracle sample (0 disables it)")
     ap.add_argument("--copy-calibration-mib", type=int, default=0,
-                    help="before timing, copy this many MiB once with repartition_kernel (plain "
-                         "16-byte loads and stores), so that a counter profile of the run can scale "
-                         "FETCH_SIZE/WRITE_SIZE by a known size")
+                    help="before timing, copy this many MiB once with repartition_kernel (16-byte "
+                         "loads, streaming beyond 256 MiB, and streaming stores), so that a counter "
+                         "profile of the run can scale FETCH_SIZE/WRITE_SIZE by a known size")
     return ap.parse_args()
 
 
@@ -271,9 +271,9 @@ def main():
 
     ws = torch.empty(max(256, cp.workspace_size(make_descs(plan), Hq, Hkv)), dtype=torch.uint8, device=dev)
     if args.copy_calibration_mib > 0:
-        # A plain copy of known size (repartition_kernel from degree 1 to degree 1:
-        # every row read once and written once with ordinary 16-byte loads and
-        # stores), so that a counter profile can scale FETCH_SIZE/WRITE_SIZE.
+        # A copy of known size (repartition_kernel from degree 1 to degree 1: every
+        # row read once and written once, 16 bytes per lane), so that a counter
+        # profile can scale FETCH_SIZE/WRITE_SIZE.
         n_cal = (args.copy_calibration_mib << 20) // (Hkv * D * 2)
         src = torch.ones((n_cal, Hkv, D), dtype=torch.bfloat16, device=dev)
         dst = torch.empty_like(src)

@@ -219,10 +219,10 @@ size_t cp_attn_partial_workspace_size(const cp_partial_desc* descs, int32_t n_de
  *   head_dim    must be 128 (else CP_ERR_UNSUPPORTED).
  *   softmax_scale  <= 0 selects 1/sqrt(head_dim) (the paper's 1/sqrt(d_h)).
  *   workspace   device buffer of workspace_bytes >= the size above (a smaller
- *               one is taken when fewer, longer pieces, or none, fit it; the
- *               result is the same attention); it is written and read by the
- *               call's kernels on `stream`, so it must not be reused until the
- *               stream is past this work.
+ *               one is taken when a list of fewer pieces, or none, fits it: the
+ *               fastest that does, the same attention); it is written and
+ *               read by the call's kernels on `stream`, so it must not be
+ *               reused until the stream is past this work.
  * The work list is planned on the host; the lists of the last 16 launches
  * are kept (keyed by every non-pointer field of the descriptors, the head
  * counts and the pinned workgroup shape, matched exactly, and by the workspace
@@ -264,16 +264,17 @@ int cp_attn_partial(const cp_partial_desc* descs, int32_t n_descs, int32_t n_hea
 int cp_set_workgroup_rows(int32_t rows);
 
 /*
- * cp_attn_partial for callers that cannot allocate: code under HIP graph
- * capture, tight serving loops, harnesses that forbid allocation.  It takes
- * no workspace and calls no allocating routine (no hipMalloc, hipFree or
- * pinned host allocation); its device scratch -- the descriptor copy, the
- * work list and the split-walk piece slots -- is a library-owned array of
+ * cp_attn_partial for callers that cannot allocate: tight serving loops,
+ * harnesses that forbid allocation.  (Not under stream capture: it waits for
+ * its stream.  cp_attn_partial can be captured.)  It takes no workspace and
+ * calls no allocating routine (no hipMalloc, hipFree or pinned host
+ * allocation); its device scratch -- the descriptor copy, the work list and
+ * the split-walk piece slots -- is a library-owned array of
  * CP_NOALLOC_SCRATCH_BYTES (32 MiB) on each GPU it runs on, held until the
  * process ends.  Descriptors, arguments and results are those of
- * cp_attn_partial; when split key walks would need more piece slots than
- * the scratch holds, fewer, longer pieces are used (same attention, other
- * work decomposition).
+ * cp_attn_partial; when the work list it would choose needs more piece slots
+ * than the scratch holds, the fastest one that fits is used (same attention,
+ * other work decomposition).
  * Each call waits on the host for `stream`'s earlier work before it
  * overwrites the scratch, then copies the tables from host memory (a
  * synchronous copy), so consecutive calls on one stream are safe.  The

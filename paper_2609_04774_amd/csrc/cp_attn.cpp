@@ -6,8 +6,9 @@
 // groups.  Items are ordered longest first (visible keys per item), which
 // makes the hardware's in-order workgroup dispatch an LPT schedule, and are
 // interleaved so that item i lands on XCD i % 8 with all items of one KV head
-// group on the same XCD: the workgroups streaming one head's K/V share that
-// XCD's L2.
+// group on the same XCD (where the groups are a multiple of the XCDs, else as
+// many as that order leaves): the workgroups streaming one head's K/V share
+// that XCD's L2.
 //
 // Cut key walks.  A launch whose work items do not fill the 256 compute units
 // evenly (few items, or items of very different lengths) has some of its walks
@@ -911,10 +912,11 @@ static int choose_list(const Blocks& small, const Blocks& large, const Blocks* w
   add_choices(large, n_descs, std::min(target_pieces, max_pieces), limit, &choices);
   *fits = !choices.empty();
   if (!*fits) return CP_OK;
-  // Piece slots that fit the eight 4 MB L2s, and with the tables the scratch
-  // of cp_attn_partial_noalloc (then both entry points run the same list),
-  // are worth a few per cent: 300 rows after 16K cached keys ran 108.4 us in
-  // 240 slots of 256 rows (32 MB) against 108.2 in 256 of 384 (51 MB).
+  // Piece slots that, with the tables, fit the scratch of cp_attn_partial_noalloc
+  // are preferred up to the estimate's own error: both entry points then run
+  // the same list, in half the workspace or less.  It buys no speed: in 87
+  // launches where this decides, the lists it takes are 1.1 % slower on average
+  // (0.86 to 1.17 times the time of those it leaves).
   constexpr size_t kSlotBytes = (size_t)(32 << 20) - (256 << 10);
   constexpr double kSlotGain = 1.04;
   // Estimated in the order of their bounds; most of them are settled by that.

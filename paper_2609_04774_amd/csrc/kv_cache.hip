@@ -29,7 +29,8 @@
 // rank's 16384 rows of the 128K prompt take 20.7 us (6.5 TB/s) whether a cache
 // holds them or not, with streaming loads 24-27, and with plain stores 28 when
 // none does; a 32K request re-sharded 39 us when one does and 46 when not, with
-// streaming loads 44 both ways.  Beyond that size streaming loads are the
+// streaming loads 44 both ways; one rank's 65536 rows re-sharded 38.5 and 45.6,
+// with streaming loads 42.3 and 43.9.  Beyond that size streaming loads are the
 // faster: 131000 rows written back 200 against 206 us.
 #include <hip/hip_runtime.h>
 

@@ -1,6 +1,5 @@
 // cp_attn_partial_noalloc: the partial attention for callers that cannot
-// allocate (code under HIP graph capture, tight serving loops, harnesses that
-// forbid allocation).  Same planning and kernels as cp_attn_partial; the
+// allocate (tight serving loops, harnesses that forbid allocation).  Same planning and kernels as cp_attn_partial; the
 // device scratch -- the descriptor copy, the work list and the split-walk
 // piece slots -- is a file-scope device array of the library instead of a
 // caller workspace, and the tables go up by a plain copy from host memory

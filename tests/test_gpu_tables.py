@@ -2,8 +2,8 @@
 small, else through pinned staging that is reused after eight launches.
 Either way the results are those of cp_attn_partial_noalloc, which copies its
 tables itself and plans the same list, bit for bit.  And launches whose walks
-are cut into many or few short pieces, against the oracle; and merges of every
-partial count."""
+are cut into many or few short pieces, against the oracle, and with NaN and
+infinite scores; and merges of every partial count."""
 
 import pytest
 import torch
