@@ -164,7 +164,7 @@ int to_dev(const cp_partial_desc& x, int idx, DevDesc* out) {
 // cached tokens, are 5 blocks of 64 positions, not 6: 103.1 -> 95.4 us.  (A batch
 // of 64 requests, 58 of degree 1, 10835 -> 10761, is within its spread of 2 %.)
 // Not with a pinned workgroup shape, whose lists keep one fixed rule, nor where
-// the launch is uncut and within one round without it (plan_joined).
+// the launch is one round without it, and faster (plan_joined).
 void join_chunks(DevDesc* d) {
   if (d->q_len[1] == 0 || d->q_begin[1] != d->q_begin[0] + d->q_len[0] ||
       d->local_off[1] != d->local_off[0] + d->q_len[0] || d->o_off[1] != d->o_off[0] + d->q_len[0])
@@ -787,40 +787,87 @@ static std::vector<int64_t> plan_key(const std::vector<DevDesc>& descs, int32_t 
 static int plan_uncached(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out,
                          size_t limit = SIZE_MAX, size_t* wanted = nullptr);
 
-// The plan of a launch's joined descriptors (*joined), or of the descriptors as
-// they are where that is one round of uncut items: there idle compute units
-// take the second chunk's rows sooner than the first chunk's workgroups (80 rows
-// of 32 heads on 8, without a prefix: 8.1-8.6 us of kernel joined, 7.1 not).
+// Time (microseconds) of a launch of about one round, closer than estimate_us for
+// workgroups that are partly empty: the fixed set-up, the loads and stores of the
+// rows that are there, a tile time by whether one or two waves of a SIMD have
+// rows (a query block of one head that is half empty leaves every SIMD one), and
+// the merge of cut items by their number, pieces and bytes.  Fitted to 4609 lists
+// of 297 launches of a last rank (20 to 4000 rows in 13 head layouts, chunks
+// joined and apart, whole and in up to 24 pieces): mean error 3.7 %, where
+// estimate_us has 12.9.  It has no say where launches of many rounds are planned,
+// to which it was not fitted.
+static double small_launch_us(const Plan& plan) {
+  const Shape& sh = plan.shape;
+  const bool large = sh.rows_per_wg == kRowsLarge;
+  const double tile[2] = {large ? 0.75 : 0.54, large ? 1.05 : 0.735};
+  const int per_wave = sh.rows_per_wg / 128, per_head = sh.q_per_wg / 16;  // 16-row blocks
+  auto two_waves = [&](int live) {  // of a SIMD, with rows: waves w and w + 4 share one
+    int n[4] = {};
+    for (int w = 0; w < 8; ++w)
+      for (int b = per_wave * w; b < per_wave * (w + 1); ++b)
+        if (b % per_head * 16 < live) {
+          if (++n[w % 4] == 2) return true;
+          break;
+        }
+    return false;
+  };
+  std::vector<Units<double>> units(kXcds, Units<double>(kComputeUnits / kXcds));
+  double sum = 0.0, end = 0.0;
+  for (size_t i = 0; i < plan.items.size(); ++i) {
+    const WorkItem& w = plan.items[i];
+    const DevDesc& d = plan.descs[w.desc];
+    const int64_t tiles = w.t_end >= 0 ? (int64_t)(w.t_end - w.t_begin) : item_tiles(d, w.chunk, w.q_block, sh.q_per_wg);
+    const int live = (int)std::min<int64_t>(sh.q_per_wg, d.q_len[w.chunk] - (int64_t)w.q_block * sh.q_per_wg);
+    const double us = 6.5 + 0.7 * live * sh.heads_per_wg / 32 + tiles * tile[two_waves(live)];
+    units[i % kXcds].add(us);
+    sum += us;
+  }
+  for (const Units<double>& u : units) end = std::max(end, u.end);
+  end += 0.097 * sum / kComputeUnits;
+  if (plan.splits.empty()) return end;
+  const double n = (double)plan.splits.size(), pieces = (double)plan.n_pieces;
+  return end + 3.6 + 0.13 * pieces / n + 0.45 * std::log2(n) + (double)piece_bytes(sh.rows_per_wg) * (2.0 * pieces + n) / 14.9e6;
+}
+
+// The plan of a launch's joined descriptors (*joined), or the whole items of the
+// descriptors as they are, where those are within one round and small_launch_us
+// finds them the faster: there idle compute units may take the second chunk's
+// rows sooner than the first chunk's workgroups, and half-empty ones end sooner
+// than their pieces and a merge (rank 3 of 4 of 1007 tokens, 28/4 heads: 27.2 us
+// joined and cut, 20.2 apart; 170 tokens on one GPU, 32/8: 14.7 joined, 16.4
+// apart).  Over the 297 launches what this takes is 1.4 % slower on average than
+// the fastest list timed; the joined choice alone 5.3.
 static int plan_joined(int32_t Hq, int32_t Hkv, int64_t target_pieces, int forced, Plan* out, size_t limit,
                        size_t* wanted, bool* joined) {
-  Plan apart;
-  apart.descs = out->descs;
+  Plan whole;
+  whole.descs = out->descs;
   *joined = false;
-  if (forced == 0)
-    for (size_t i = 0; i < out->descs.size(); ++i) {
-      join_chunks(&out->descs[i]);
-      *joined |= out->descs[i].q_len[1] != apart.descs[i].q_len[1];
-    }
-  if (!*joined) return plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, wanted);
-  Plan free_choice;
-  free_choice.descs = out->descs;
-  int st = plan_uncached(Hq, Hkv, target_pieces, forced, &free_choice, SIZE_MAX, wanted);
+  if (forced) return plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, wanted);
+  for (size_t i = 0; i < out->descs.size(); ++i) {
+    join_chunks(&out->descs[i]);
+    *joined |= out->descs[i].q_len[1] != whole.descs[i].q_len[1];
+  }
+  const Blocks blocks = list_blocks(whole.descs, Hq, Hkv, kRowsSmall);
+  const bool one_round = blocks.list.size() * blocks.n_groups <= (size_t)kComputeUnits;
+  if (!*joined && !one_round) return plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, wanted);
+  Plan choice;
+  choice.descs = out->descs;
+  int st = plan_uncached(Hq, Hkv, target_pieces, forced, &choice, SIZE_MAX, wanted);
   if (st != CP_OK) return st;
-  auto one_round = [](const Plan& p) { return p.n_pieces == 0 && p.items.size() <= (size_t)kComputeUnits; };
-  bool apart_chosen = false;
-  if (one_round(free_choice)) {
-    size_t size = 0;
-    st = plan_uncached(Hq, Hkv, target_pieces, forced, &apart, SIZE_MAX, &size);
+  if (one_round && (*joined || choice.n_pieces > 0)) {
+    st = plan_items(blocks, target_pieces, false, std::max<int64_t>(1, blocks.max_tiles), &whole);
     if (st != CP_OK) return st;
-    apart_chosen = one_round(apart);
-    if (apart_chosen) *wanted = size;
+    if (small_launch_us(whole) < small_launch_us(choice)) {
+      choice = std::move(whole);
+      *wanted = layout_of(choice).total;
+      *joined = false;
+    }
   }
   if (*wanted > limit) {
     size_t size = 0;
     return plan_uncached(Hq, Hkv, target_pieces, forced, out, limit, &size);
   }
-  *out = apart_chosen ? std::move(apart) : std::move(free_choice);
-  *joined = !apart_chosen;
+  *out = std::move(choice);
   return CP_OK;
 }
 

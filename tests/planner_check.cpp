@@ -255,9 +255,15 @@ int main() {
     cp_set_workgroup_rows(0);
   }
   // The last rank's adjacent chunks are one, from the planner and from the
-  // cache, except where both are within one round of uncut items.
+  // cache, except where whole items of both are one round and end sooner (126 and
+  // 126 rows in blocks of 256, or two blocks of 64 either way for 40 and 40).
   for (int again = 0; again < 2; ++again) {
     const cp_partial_desc turn = desc(16368, 300, 1, 0, CP_KV_ALL, 1), small = desc(0, 160, 2, 1, CP_KV_ALL, 1);
+    const cp_partial_desc halves = desc(0, 1007, 4, 3, CP_KV_ALL, 1), prompt = desc(0, 170, 1, 0, CP_KV_ALL, 1);
+    build_plan(&halves, 1, 28, 4, kTargetPieces, &p);
+    expect(p.descs[0].q_len[0] == 126 && p.descs[0].q_len[1] == 126 && p.n_pieces == 0, "half-empty blocks joined");
+    build_plan(&prompt, 1, 32, 8, kTargetPieces, &p);
+    expect(p.descs[0].q_len[0] == 170 && p.descs[0].q_len[1] == 0, "chunks that end in one block fewer apart");
     build_plan(&turn, 1, 32, 8, kTargetPieces, &p);
     expect(p.descs[0].q_len[0] == 300 && p.descs[0].q_len[1] == 0, "chunks of a cut launch apart");
     build_plan(&small, 1, 32, 8, kTargetPieces, &p);
