@@ -547,6 +547,16 @@ int plan_items(const Blocks& b_, int64_t target_pieces, bool pinned, int64_t cap
     }
   }
   if (total > 0x7fffffffLL) return fail(CP_ERR_UNSUPPORTED, "cp_attn_partial: work list beyond 2^31 workgroups");
+  // One round of lists that are not alike: one list, in the order of the lengths,
+  // so that every XCD takes items of every group (all start at once: no XCD has
+  // more than its share).  2207 tokens, rank 0 of 2, 8/2 heads: 27.2 us, 29.1 with a
+  // group on every other XCD; 156 launches of up to 60 us 0.4 % faster on average.
+  // Longer ones keep the lists: 0.2 % faster beyond 500 us, up to 2 %.
+  if (schedules_of(n_groups) == 1 && total <= kComputeUnits)
+    for (int x = 1; x < kXcds; ++x) {
+      per_xcd[0].insert(per_xcd[0].end(), per_xcd[x].begin(), per_xcd[x].end());
+      per_xcd[x].clear();
+    }
   for (auto& v : per_xcd)
     std::stable_sort(v.begin(), v.end(), [](const Cand& a, const Cand& b) { return a.cost > b.cost; });
   out->items.clear();
