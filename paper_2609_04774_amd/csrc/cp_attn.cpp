@@ -243,19 +243,29 @@ struct Units {
   }
 };
 
-// Makespan of list scheduling `lens` (sorted longest first) onto `n` units; or,
-// as soon as it is known to exceed `give_up`, something above that.
-int64_t list_schedule(int n, const std::vector<int64_t>& lens, int64_t give_up = INT64_MAX) {
+// Makespan of list scheduling `lens` (sorted longest first) onto units whose
+// loads start at `loads`; or, as soon as it is known to exceed `give_up`,
+// something above that.
+int64_t list_schedule(const std::vector<int64_t>& loads, const std::vector<int64_t>& lens,
+                      int64_t give_up = INT64_MAX) {
   // Of the r * n + 1 longest, some of n units takes r + 1: the shortest r + 1
   // of them at least.
+  const size_t n = loads.size();
   for (size_t r = 1; give_up != INT64_MAX && r * n < lens.size(); ++r) {
     int64_t t = 0;
     for (size_t i = r * n - r; i <= r * n; ++i) t += lens[i] + kItemSetupTiles;
     if (t > give_up) return t;
   }
-  Units<int64_t> units(n);
+  Units<int64_t> units(0);
+  units.free = loads;
+  std::make_heap(units.free.begin(), units.free.end(), std::greater<int64_t>());
+  units.end = *std::max_element(loads.begin(), loads.end());
+  const bool idle = units.end == 0;
   for (size_t k = 0; k < lens.size(); ++k) {
-    units.add_sorted(k, lens[k] + kItemSetupTiles);
+    if (idle)
+      units.add_sorted(k, lens[k] + kItemSetupTiles);
+    else
+      units.add(lens[k] + kItemSetupTiles);
     if (units.end > give_up) break;
   }
   return units.end;
@@ -385,10 +395,11 @@ void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_ite
   std::vector<size_t> order(items.size());  // longest first
   std::iota(order.begin(), order.end(), (size_t)0);
   std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return items[a].tiles > items[b].tiles; });
+  const std::vector<int64_t> idle(n_units, 0);
   std::vector<int64_t> lens;
   for (size_t i : order) lens.push_back(items[i].tiles);
   // The best makespan and its piece count.
-  std::pair<int64_t, int64_t> best(list_schedule(n_units, lens), 0);
+  std::pair<int64_t, int64_t> best(list_schedule(idle, lens), 0);
   if (best.first <= limit) return;
   Candidate chosen;
   auto consider = [&](Candidate c) {
@@ -398,7 +409,7 @@ void balance_cuts(const std::vector<ItemTiles>& items, int n_units, size_t n_ite
     std::sort(c.pieces.begin(), c.pieces.end(), std::greater<int64_t>());
     lens.resize(c.pieces.size() + c.whole.size());
     std::merge(c.pieces.begin(), c.pieces.end(), c.whole.begin(), c.whole.end(), lens.begin(), std::greater<int64_t>());
-    const std::pair<int64_t, int64_t> sc(list_schedule(n_units, lens, best.first), n_pieces);
+    const std::pair<int64_t, int64_t> sc(list_schedule(idle, lens, best.first), n_pieces);
     if (sc < best) {
       best = sc;
       chosen = std::move(c);
